@@ -141,7 +141,7 @@ struct Workspace {
     // distinct counts, long segments' offsets, their sort keys and results
     DevBuf a_voff, a_seg, a_cnt, a_hoff, a_uoff, h_keys, h_keys_alt, h_col, h_wt;
     // per-graph state of a level (G entries) and sweep control
-    DevBuf ctl, gdone, gsweeps, gmoves, gactive, gsum, gsq, gmeta, segs;
+    DevBuf ctl, ctr, gdone, gsweeps, gmoves, gactive, gsum, gsq, gmeta, segs;
 };
 
 struct Timer {
@@ -711,6 +711,7 @@ lv_status run_sweeps(lv_graph* g, const LevelGraph& G, int mode, const Params& p
     HIP_TRY(ws.tmp.ensure(std::max(radix_tmp_bytes(n), scan_tmp_bytes(n, 8))));
     HIP_TRY(ws.small.ensure(4096));
     HIP_TRY(ws.ctl.ensure(sizeof(SweepCtl)));
+    HIP_TRY(ws.ctr.ensure(sizeof(SweepCounters)));
     HIP_TRY(ws.gdone.ensure(sizeof(int32_t) * (size_t)G.G));
     HIP_TRY(ws.gsweeps.ensure(sizeof(int32_t) * (size_t)G.G));
     HIP_TRY(ws.gmoves.ensure(sizeof(uint32_t) * (size_t)G.G * (size_t)S));
@@ -798,7 +799,7 @@ lv_status run_sweeps(lv_graph* g, const LevelGraph& G, int mode, const Params& p
     }
     const int32_t* act_verts = vert_sorted + start[CLS_L4];  // vertices with entries (the only pairs ever gathered)
     HIP_TRY(launch_pairs(active, act_verts, ws.comm.as<int32_t>(), ws.sigma.as<int32_t>(), ws.cs.as<int2>(), nullptr, s));
-    HIP_TRY(launch_ctl_init(ctl, G.G, gactive, ws.gdone.as<int32_t>(), ws.gsweeps.as<int32_t>(),
+    HIP_TRY(launch_ctl_init(ctl, ws.ctr.as<SweepCounters>(), G.G, gactive, ws.gdone.as<int32_t>(), ws.gsweeps.as<int32_t>(),
                             ws.gmoves.as<uint32_t>(), S, s));
 
     MoveArgs a{};
@@ -831,6 +832,10 @@ lv_status run_sweeps(lv_graph* g, const LevelGraph& G, int mode, const Params& p
     a.mark = mark;
     int32_t* dec_all = ws.dec.as<int32_t>();
     const int64_t theta = mode == MODE_LPA ? p.lpa_threshold : 0;
+    // synchronous sweeps alternate direction, so a level ends after two
+    // quiet sweeps; an asynchronous level ends after one (Alg. 2's test)
+    const SweepEnd end{ctl, ws.ctr.as<SweepCounters>(), G.G, ws.gdone.as<int32_t>(), ws.gsweeps.as<int32_t>(),
+                       ws.gmoves.as<uint32_t>(), S, theta, async ? 1 : 2, ec_read_max, ec_fill_max};
 
     Timer tm;
     tm.on = timing;
@@ -886,20 +891,19 @@ lv_status run_sweeps(lv_graph* g, const LevelGraph& G, int mode, const Params& p
         }
         if (!async) {  // asynchronous sweeps have moved already
             HIP_TRY(launch_apply(act_verts, dec_all + start[CLS_L4], active, G.k, a.gid, ws.comm.as<int32_t>(),
-                                 mode == MODE_LPA ? nullptr : ws.sigma.as<int32_t>(), ctl, ws.gmoves.as<uint32_t>(),
-                                 S, s));
+                                 mode == MODE_LPA ? nullptr : ws.sigma.as<int32_t>(), ctl, ws.ctr.as<SweepCounters>(),
+                                 ws.gmoves.as<uint32_t>(), S, s));
+            // the pair refresh's last workgroup ends the sweep
             if (use_ec)
                 HIP_TRY(launch_pairs_changed(active, nonhub, act_verts, G.off, ws.comm.as<int32_t>(),
                                              ws.sigma.as<int32_t>(), ws.cs.as<int2>(), ws.chg.as<uint8_t>(),
-                                             ws.rlist.as<int4>(), ws.rcnt.as<int32_t>(), mode, ctl, s));
+                                             ws.rlist.as<int4>(), ws.rcnt.as<int32_t>(), mode, end, s));
             else
                 HIP_TRY(launch_pairs(active, act_verts, ws.comm.as<int32_t>(), ws.sigma.as<int32_t>(),
-                                     ws.cs.as<int2>(), ctl, s));
+                                     ws.cs.as<int2>(), &end, s));
+        } else {
+            HIP_TRY(launch_sweep_end(end, s));
         }
-        // synchronous sweeps alternate direction, so a level ends after two
-        // quiet sweeps; an asynchronous level ends after one (Alg. 2's test)
-        HIP_TRY(launch_sweep_end(ctl, G.G, ws.gdone.as<int32_t>(), ws.gsweeps.as<int32_t>(),
-                                 ws.gmoves.as<uint32_t>(), S, theta, async ? 1 : 2, ec_read_max, ec_fill_max, s));
         if (e) HIP_TRY(tm.mark(&(*e)[2 * NUM_CLS + 4]));
         if (use_ec) {  // rewrite the changed entries if the next sweep reads the cache
             HIP_TRY(launch_cache_refresh(active, ws.rlist.as<int4>(), ws.rcnt.as<int32_t>(), G.rev,

@@ -138,7 +138,11 @@ struct GraphAcc {
 
 // Merge-path tiles visited by each workgroup of a grid of at most this many
 // (fewer workgroups, fewer atomics on the per-graph sums)
-constexpr unsigned SUM_GRID = 2048;
+constexpr unsigned SUM_GRID = 1024;
+// Workgroups of the per-vertex sums: each ends in one atomic on one address,
+// and those are served one after another (about 13 ns each: 4096 workgroups
+// took 52 us over 2 M vertices).
+constexpr int64_t VSUM_GRID = 512;
 
 // out[g] += sum of v_i^2 (or v_i) over the vertices of graph g (gid null: one graph)
 template <bool SQUARE>
@@ -253,12 +257,18 @@ __global__ void k_degree_keys(int32_t n, const int32_t* off, const int32_t* gid,
 }
 __global__ __launch_bounds__(256) void k_max_degree(int32_t n, const int32_t* off, int32_t* out)
 {
+    __shared__ int32_t red[256 / WAVE];
     int32_t m = 0;
     for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < n; v += (int64_t)gridDim.x * 256)
         m = max(m, off[v + 1] - off[v]);
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) m = max(m, __shfl_xor(m, d));
-    if (lane_id() == 0) atomicMax(out, m);
+    if (lane_id() == 0) red[threadIdx.x / WAVE] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 256 / WAVE; ++w) m = max(m, red[w]);
+        atomicMax(out, m);
+    }
 }
 __global__ void k_inverse(const int32_t* perm, int32_t n, int32_t* inv)
 {
@@ -337,7 +347,7 @@ hipError_t launch_degree_keys(int32_t n, const int32_t* off, const int32_t* gid,
 hipError_t launch_max_degree(int32_t n, const int32_t* off, int32_t* out, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    k_max_degree<<<grid_for(n, 256, 4096), 256, 0, s>>>(n, off, out);
+    k_max_degree<<<grid_for(n, 256, VSUM_GRID), 256, 0, s>>>(n, off, out);
     return hipGetLastError();
 }
 hipError_t launch_inverse(const int32_t* perm, int32_t n, int32_t* inv, hipStream_t s)
@@ -423,7 +433,7 @@ hipError_t launch_row_sums(int32_t n, const int32_t* off, const int32_t* w, int6
     if (e != hipSuccess) return e;
     if (nnz > 0) k_row_sums<<<tiles_for(n, nnz), TILE_BS, 0, s>>>(n, off, w, nnz, (unsigned long long*)k64);
     if (n > 0)
-        k_narrow_sum<<<grid_for(n, 256, 4096), 256, 0, s>>>(n, (const unsigned long long*)k64, k,
+        k_narrow_sum<<<grid_for(n, 256, VSUM_GRID), 256, 0, s>>>(n, (const unsigned long long*)k64, k,
                                                             (unsigned long long*)total);
     return hipGetLastError();
 }
@@ -435,12 +445,12 @@ hipError_t launch_degree_unit(int32_t n, const int32_t* off, int32_t* k, hipStre
 }
 hipError_t launch_sum_sq(const int32_t* v, int64_t n, const int32_t* gid, int64_t* out, hipStream_t s)
 {
-    if (n > 0) k_sum_sq<true><<<grid_for(n, 256, 4096), 256, 0, s>>>(n, v, gid, (unsigned long long*)out);
+    if (n > 0) k_sum_sq<true><<<grid_for(n, 256, VSUM_GRID), 256, 0, s>>>(n, v, gid, (unsigned long long*)out);
     return hipGetLastError();
 }
 hipError_t launch_seg_sum(const int32_t* v, int64_t n, const int32_t* gid, int64_t* out, hipStream_t s)
 {
-    if (n > 0) k_sum_sq<false><<<grid_for(n, 256, 4096), 256, 0, s>>>(n, v, gid, (unsigned long long*)out);
+    if (n > 0) k_sum_sq<false><<<grid_for(n, 256, VSUM_GRID), 256, 0, s>>>(n, v, gid, (unsigned long long*)out);
     return hipGetLastError();
 }
 hipError_t launch_fill_gid(const int32_t* voff, int32_t G, int32_t n, int32_t* gid, hipStream_t s)
@@ -478,7 +488,7 @@ hipError_t launch_modularity_parts(int32_t n, const int32_t* off, const int32_t*
         k_sigma_in<<<std::min(tiles_for(n, nnz), SUM_GRID), TILE_BS, 0, s>>>(n, off, idx, w, nnz, labels, nullptr,
                                                          (unsigned long long*)out2);
     if (n > 0)
-        k_sum_sq_u64<<<grid_for(n, 256, 4096), 256, 0, s>>>((const unsigned long long*)tot, n,
+        k_sum_sq_u64<<<grid_for(n, 256, VSUM_GRID), 256, 0, s>>>((const unsigned long long*)tot, n,
                                                             (unsigned long long*)(out2 + 1));
     return hipGetLastError();
 }

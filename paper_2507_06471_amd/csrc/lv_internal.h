@@ -55,12 +55,43 @@ struct SweepCtl {
     // EC_FILL the same and also storing it into ce[e], EC_READ from ce[e].
     int32_t ec_mode;
     int32_t ec_reads;                 // sweeps of this level that read the cache
-    unsigned long long chg_entries;   // entries whose pair the last commit changed
     unsigned long long refreshed;     // entries rewritten by cache refreshes this level
     int32_t work_next;                // next work item of the fused sweep kernel
     int32_t ec_last;                  // how the last completed sweep got its pairs
 };
 constexpr int32_t EC_GATHER = 0, EC_FILL = 1, EC_READ = 2;
+
+// Counters that every workgroup of a commit adds to, spread over CTR_WAYS
+// cache lines (workgroup b uses way b % CTR_WAYS): same-address atomics from
+// many workgroups are served one after another (about 13 ns each, since they
+// cross the XCDs' L2s), so a single counter cost a launch of 8192 workgroups
+// over 100 us.  All zero between sweeps: the sweep's last workgroup takes the
+// sums out.
+constexpr int CTR_WAYS = 64;
+struct SweepCounters {
+    struct alignas(128) Way {
+        unsigned long long chg;  // entries whose pair changed in this commit
+        uint32_t moves;          // movers of this sweep (one graph)
+        uint32_t ticket;         // workgroups of this way that are done
+    } way[CTR_WAYS];
+    alignas(128) uint32_t ways_done;
+};
+
+// What ends a sweep (k_sweep_end's arguments), run by the last workgroup of
+// the pair refresh.
+struct SweepEnd {
+    SweepCtl* ctl;
+    SweepCounters* ctr;
+    int32_t G;
+    int32_t* gdone;
+    int32_t* gsweeps;
+    uint32_t* gmoves;
+    int32_t max_sweeps;
+    int64_t theta;
+    int32_t consecutive;
+    int64_t ec_read_max;    // the next sweep reads the entry cache if it was filled and at most this
+    int64_t ec_fill_max;    // many entries changed, else fills it if at most ec_fill_max did (-1: no cache)
+};
 
 // Arguments shared by every move kernel.
 struct MoveArgs {
@@ -278,16 +309,18 @@ hipError_t launch_probe_gather(const int32_t* idx, const int2* tab, int64_t nnz,
 hipError_t launch_mark_movers(const int4* rows, const int32_t* dec, int32_t m, const int32_t* idx, int32_t* mark,
                               const SweepCtl* ctl, hipStream_t s);
 hipError_t launch_hub_mark(const MoveArgs& a, const HubArgs& h, int32_t* mark, hipStream_t s);
+// cs[v] = (comm[v], sigma[comm[v]]) for the listed vertices; end (may be null):
+// the last workgroup to finish ends the sweep (see k_sweep_end)
 hipError_t launch_pairs(int32_t n, const int32_t* verts, const int32_t* comm, const int32_t* sigma, int2* cs,
-                        const SweepCtl* ctl, hipStream_t s);
+                        const SweepEnd* end, hipStream_t s);
 // As launch_pairs over the m listed vertices verts[0..m) (class order), also
 // recording in chg[t] whether slot t's pair changed (LPA: its label) and
-// adding the changed rows' entries to ctl->chg_entries.  The changed rows of
+// summing the changed rows' entries for the sweep's end.  The changed rows of
 // slots below `nonhub` are listed per 256-slot tile: (row begin, length, new
 // pair) at list[tile * 256 + i] for i < cnt[tile].
 hipError_t launch_pairs_changed(int32_t m, int32_t nonhub, const int32_t* verts, const int32_t* off,
                                 const int32_t* comm, const int32_t* sigma, int2* cs, uint8_t* chg, int4* list,
-                                int32_t* cnt, int mode, SweepCtl* ctl, hipStream_t s);
+                                int32_t* cnt, int mode, const SweepEnd& end, hipStream_t s);
 // Entry-cache refresh when the next sweep reads the cache: for every listed
 // changed row (list/cnt of launch_pairs_changed over m slots), ce[rev[e]] =
 // its new pair for each non-loop entry e of the row.  Hubs: through their
@@ -304,23 +337,19 @@ hipError_t launch_reverse_rank(int32_t n, const int32_t* off, const int32_t* idx
 // rev[e] = off[idx[e]] + rank[e] (rows kept in place)
 hipError_t launch_reverse_from_rank(int32_t n, const int32_t* off, const int32_t* idx, int64_t nnz,
                                     const int32_t* rank, int32_t* rev, hipStream_t s);
-// commit the decisions dec[0..m) of vertices verts[0..m); per-graph movers into
-// gmoves; sigma null: labels only (LPA)
+// commit the decisions dec[0..m) of vertices verts[0..m); movers into
+// ctr (one graph) or per graph into gmoves; sigma null: labels only (LPA)
 hipError_t launch_apply(const int32_t* verts, const int32_t* dec, int32_t m, const int32_t* k, const int32_t* gid,
-                        int32_t* comm, int32_t* sigma, const SweepCtl* ctl, uint32_t* gmoves, int32_t max_sweeps,
-                        hipStream_t s);
+                        int32_t* comm, int32_t* sigma, const SweepCtl* ctl, SweepCounters* ctr, uint32_t* gmoves,
+                        int32_t max_sweeps, hipStream_t s);
 // sigma[comm[v]] += k[v] for the vertices verts[0..m) (the caller clears sigma)
 hipError_t launch_volumes(const int32_t* verts, int32_t m, const int32_t* k, const int32_t* comm, int32_t* sigma,
                           hipStream_t s);
 // level start: sweep counter 0; gdone[g] = !gactive[g] (gactive null = all run); moves zeroed
-hipError_t launch_ctl_init(SweepCtl* ctl, int32_t G, const int32_t* gactive, int32_t* gdone, int32_t* gsweeps,
-                           uint32_t* gmoves, int32_t max_sweeps, hipStream_t s);
-// ec_read_max / ec_fill_max: the next sweep reads the entry cache if it was
-// filled and at most ec_read_max entries changed, else fills it if at most
-// ec_fill_max changed (-1: no cache)
-hipError_t launch_sweep_end(SweepCtl* ctl, int32_t G, int32_t* gdone, int32_t* gsweeps, const uint32_t* gmoves,
-                            int32_t max_sweeps, int64_t theta, int32_t consecutive, int64_t ec_read_max,
-                            int64_t ec_fill_max, hipStream_t s);
+hipError_t launch_ctl_init(SweepCtl* ctl, SweepCounters* ctr, int32_t G, const int32_t* gactive, int32_t* gdone,
+                           int32_t* gsweeps, uint32_t* gmoves, int32_t max_sweeps, hipStream_t s);
+// the end of a sweep as a launch of its own (asynchronous sweeps refresh no pairs)
+hipError_t launch_sweep_end(const SweepEnd& end, hipStream_t s);
 
 // renumber + aggregation
 hipError_t launch_renumber(int32_t n, const int32_t* comm, const int32_t* orig, int32_t* minv, int32_t* flag,

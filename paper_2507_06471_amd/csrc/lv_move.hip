@@ -1275,9 +1275,14 @@ __device__ __forceinline__ void peeled_apply(int32_t* key, int32_t* val, int32_t
 // (sigma not null) the community volumes follow.  LPA passes no volumes: its
 // scores never read them, and they are summed once from the final labels
 // (k_volumes).
+// Each workgroup takes a contiguous run of 256-slot tiles: in a packed handle
+// consecutive slots of a class belong to one graph, so a thread's running
+// mover count is rarely flushed.  The movers of a single graph go to the
+// workgroup's way of the spread counters (2048 workgroups adding to one
+// address took 27 us, more than the rest of a late sweep's commit).
 __global__ __launch_bounds__(256) void k_apply(const int32_t* verts, const int32_t* dec, int32_t m, const int32_t* k,
                                                const int32_t* gid, int32_t* comm, int32_t* sigma, const SweepCtl* ctl,
-                                               uint32_t* gmoves, int32_t max_sweeps)
+                                               SweepCounters* ctr, uint32_t* gmoves, int32_t max_sweeps)
 {
     __shared__ int32_t t_key[APPLY_SLOTS];
     __shared__ int32_t t_val[APPLY_SLOTS];
@@ -1289,7 +1294,9 @@ __global__ __launch_bounds__(256) void k_apply(const int32_t* verts, const int32
     uint32_t* moves = gmoves + ctl->sweep;
     int64_t my_g = -1;  // this thread's running mover count, for graph my_g
     uint32_t my_n = 0;
-    for (int64_t base = (int64_t)blockIdx.x * 256; base < m; base += (int64_t)gridDim.x * 256) {
+    const int64_t tiles = ((int64_t)m + 255) / 256;
+    const int64_t t_end = tiles * ((int64_t)blockIdx.x + 1) / gridDim.x * 256;
+    for (int64_t base = tiles * (int64_t)blockIdx.x / gridDim.x * 256; base < t_end; base += 256) {
         const int64_t t = base + threadIdx.x;
         const int32_t C = t < m ? dec[t] : -1;
         const bool valid = C >= 0;
@@ -1316,7 +1323,13 @@ __global__ __launch_bounds__(256) void k_apply(const int32_t* verts, const int32
     if (sigma)
         for (int t = threadIdx.x; t < APPLY_SLOTS; t += 256)
             if (t_key[t] != EMPTY_KEY && t_val[t] != 0) atomicAdd(&sigma[t_key[t]], t_val[t]);
-    block_flush_sums<256, uint32_t>(moves, my_n ? my_g : -1, my_n);
+    if (gid) {
+        block_flush_sums<256, uint32_t>(moves, my_n ? my_g : -1, my_n);
+    } else {
+        __shared__ uint32_t red[4];
+        const uint32_t n = block_sum<256>(my_n, red);
+        if (threadIdx.x == 0 && n) atomicAdd(&ctr->way[blockIdx.x % CTR_WAYS].moves, n);
+    }
 }
 
 // sigma[comm[v]] += k[v] over the listed vertices verts[0..m) (sigma cleared
@@ -1354,46 +1367,95 @@ __global__ __launch_bounds__(256) void k_volumes(const int32_t* verts, int32_t m
 // most ec_read_max entries saw their pair change in this commit (the refresh
 // that follows rewrites them), else by gathering, filling the cache on the way
 // if at most ec_fill_max entries changed (a later sweep may then read it).
-__global__ __launch_bounds__(256) void k_sweep_end(SweepCtl* ctl, int32_t G, int32_t* gdone, int32_t* gsweeps,
-                                                   const uint32_t* gmoves, int32_t max_sweeps, int64_t theta,
-                                                   int32_t consecutive, int64_t ec_read_max, int64_t ec_fill_max)
+// Called by one whole workgroup, after every other workgroup of the commit has
+// added to the counters (which it takes out and leaves zero).
+template <int BS>
+__device__ __forceinline__ void end_sweep(const SweepEnd& p)
 {
-    __shared__ int32_t red[4];
-    if (ctl->all_done) return;
+    __shared__ int32_t red[BS / WAVE];
+    __shared__ unsigned long long s_chg;
+    SweepCtl* ctl = p.ctl;
     const int32_t s = ctl->sweep + 1;
-    int32_t running = 0;
-    for (int32_t g = threadIdx.x; g < G; g += 256) {
-        if (gdone[g]) continue;
-        const uint32_t* mv = gmoves + (int64_t)g * max_sweeps;
-        bool quiet = s >= consecutive;
-        for (int32_t q = 1; q <= consecutive && quiet; ++q) quiet = (int64_t)mv[s - q] <= theta;
-        const bool stop = quiet || s >= max_sweeps;
-        if (stop) { gdone[g] = 1; gsweeps[g] = s; } else ++running;
+    static_assert(CTR_WAYS == WAVE, "one lane of the first wavefront takes each way");
+    if (threadIdx.x < WAVE) {
+        unsigned long long chg = atomicExch(&p.ctr->way[threadIdx.x].chg, 0ull);
+        uint32_t mv = atomicExch(&p.ctr->way[threadIdx.x].moves, 0u);
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) {
+            chg += __shfl_xor(chg, d);
+            mv += __shfl_xor(mv, d);
+        }
+        if (threadIdx.x == 0) {
+            s_chg = chg;
+            if (mv) p.gmoves[s - 1] = mv;  // one graph: counted by ways
+        }
     }
-    running = block_sum<256>(running, red);
+    __syncthreads();
+    int32_t running = 0;
+    for (int32_t g = threadIdx.x; g < p.G; g += BS) {
+        if (p.gdone[g]) continue;
+        const uint32_t* mv = p.gmoves + (int64_t)g * p.max_sweeps;
+        bool quiet = s >= p.consecutive;
+        for (int32_t q = 1; q <= p.consecutive && quiet; ++q) quiet = (int64_t)mv[s - q] <= p.theta;
+        const bool stop = quiet || s >= p.max_sweeps;
+        if (stop) { p.gdone[g] = 1; p.gsweeps[g] = s; } else ++running;
+    }
+    running = block_sum<BS>(running, red);
     if (threadIdx.x == 0) {
         ctl->sweep = s;
         ctl->all_done = running == 0 ? 1 : 0;
         ctl->work_next = 0;
-        if (ec_read_max >= 0) {
+        if (p.ec_read_max >= 0) {
             ctl->ec_last = ctl->ec_mode;
-            const unsigned long long chg = ctl->chg_entries;
+            const unsigned long long chg = s_chg;
             const bool filled = ctl->ec_mode != EC_GATHER;
             int32_t next = EC_GATHER;
-            if (filled && chg <= (unsigned long long)ec_read_max) next = EC_READ;
-            else if (chg <= (unsigned long long)ec_fill_max) next = EC_FILL;
+            if (filled && chg <= (unsigned long long)p.ec_read_max) next = EC_READ;
+            else if (chg <= (unsigned long long)p.ec_fill_max) next = EC_FILL;
             ctl->ec_mode = next;
             if (next == EC_READ && running > 0) {
                 ctl->ec_reads += 1;
                 ctl->refreshed += chg;
             }
-            ctl->chg_entries = 0;
         }
     }
 }
 
-__global__ void k_ctl_init(SweepCtl* ctl, int32_t G, const int32_t* gactive, int32_t* gdone, int32_t* gsweeps,
-                           uint32_t* gmoves, int32_t max_sweeps)
+// Whether this workgroup is the last of its launch to get here; every thread
+// of every workgroup calls it once.  Tickets are counted per way first, so
+// that no counter takes more than gridDim.x / CTR_WAYS + 1 same-address
+// atomics.  No workgroup waits for another.  Thread 0's earlier atomics on
+// the counters have completed when its ticket is taken; other memory that the
+// workgroups of this launch wrote is not ordered by it.
+__device__ __forceinline__ bool last_workgroup(SweepCounters* ctr)
+{
+    __shared__ int32_t s_last;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t w = blockIdx.x % CTR_WAYS;
+        const uint32_t mine = (gridDim.x - w + CTR_WAYS - 1u) / CTR_WAYS;
+        const uint32_t ways = min(gridDim.x, (uint32_t)CTR_WAYS);
+        __builtin_amdgcn_s_waitcnt(0);
+        bool last = atomicAdd(&ctr->way[w].ticket, 1u) + 1u == mine;
+        if (last) {
+            atomicExch(&ctr->way[w].ticket, 0u);
+            last = atomicAdd(&ctr->ways_done, 1u) + 1u == ways;
+            if (last) atomicExch(&ctr->ways_done, 0u);
+        }
+        s_last = last ? 1 : 0;
+    }
+    __syncthreads();
+    return s_last != 0;
+}
+
+__global__ __launch_bounds__(256) void k_sweep_end(SweepEnd p)
+{
+    if (p.ctl->all_done) return;
+    end_sweep<256>(p);
+}
+
+__global__ void k_ctl_init(SweepCtl* ctl, SweepCounters* ctr, int32_t G, const int32_t* gactive, int32_t* gdone,
+                           int32_t* gsweeps, uint32_t* gmoves, int32_t max_sweeps)
 {
     const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t t = t0; t < (int64_t)G * max_sweeps; t += stride) gmoves[t] = 0;
@@ -1401,30 +1463,40 @@ __global__ void k_ctl_init(SweepCtl* ctl, int32_t G, const int32_t* gactive, int
         gdone[g] = gactive && !gactive[g] ? 1 : 0;
         gsweeps[g] = 0;
     }
+    if (t0 < CTR_WAYS) {
+        ctr->way[t0].chg = 0;
+        ctr->way[t0].moves = 0;
+        ctr->way[t0].ticket = 0;
+    }
     if (t0 == 0) {
+        ctr->ways_done = 0;
         ctl->sweep = 0;
         ctl->all_done = 0;
         ctl->ec_mode = EC_GATHER;
         ctl->ec_last = EC_GATHER;
         ctl->ec_reads = 0;
         ctl->work_next = 0;
-        ctl->chg_entries = 0;
         ctl->refreshed = 0;
     }
 }
 
 // cs[v] = (comm[v], Sigma_tot(comm[v])): the pair a move kernel gathers per
 // CSR entry, for the listed vertices (verts null: v < n).  Only vertices with
-// entries need it: nobody gathers an isolated vertex's pair.
-__global__ void k_pairs(int32_t n, const int32_t* verts, const int32_t* comm, const int32_t* sigma, int2* cs,
-                        const SweepCtl* ctl)
+// entries need it: nobody gathers an isolated vertex's pair.  END: the last
+// workgroup ends the sweep, which saves a launch of one workgroup per sweep
+// (4 us with the gap before it).
+template <bool END>
+__global__ __launch_bounds__(256) void k_pairs(int32_t n, const int32_t* verts, const int32_t* comm,
+                                               const int32_t* sigma, int2* cs, SweepEnd end)
 {
-    if (ctl && ctl->all_done) return;
+    if (END && end.ctl->all_done) return;
     for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x) {
         const int32_t v = verts ? verts[t] : (int32_t)t;
         const int32_t c = comm[v];
         cs[v] = make_int2(c, sigma[c]);
     }
+    if constexpr (END)
+        if (last_workgroup(end.ctr)) end_sweep<256>(end);
 }
 
 // As k_pairs over the listed vertices (class order), recording whether each
@@ -1438,11 +1510,11 @@ __global__ void k_pairs(int32_t n, const int32_t* verts, const int32_t* comm, co
 __global__ __launch_bounds__(256) void k_pairs_changed(int32_t m, int32_t nonhub, const int32_t* __restrict__ verts,
                                                        const int32_t* __restrict__ off, const int32_t* comm,
                                                        const int32_t* sigma, int2* cs, uint8_t* chg, int4* list,
-                                                       int32_t* cnt, int mode, SweepCtl* ctl)
+                                                       int32_t* cnt, int mode, SweepEnd end)
 {
     __shared__ unsigned long long red[4];
     __shared__ int32_t w_cnt[4];
-    if (ctl->all_done) return;
+    if (end.ctl->all_done) return;
     unsigned long long tot = 0;
     for (int64_t base = (int64_t)blockIdx.x * 256; base < m; base += (int64_t)gridDim.x * 256) {
         const int64_t t = base + threadIdx.x;
@@ -1476,9 +1548,11 @@ __global__ __launch_bounds__(256) void k_pairs_changed(int32_t m, int32_t nonhub
         __syncthreads();  // w_cnt is reused by the next tile
     }
     tot = block_sum<256>(tot, red);
-    if (threadIdx.x == 0 && tot) atomicAdd(&ctl->chg_entries, tot);
+    if (threadIdx.x == 0 && tot) atomicAdd(&end.ctr->way[blockIdx.x % CTR_WAYS].chg, tot);
+    if (last_workgroup(end.ctr)) end_sweep<256>(end);
 }
 
+constexpr int32_t COMMIT_GRID = 8192;   // workgroups of a pair refresh at most
 constexpr int32_t REFRESH_GRID = 8192;  // four rounds of resident 256-thread workgroups
 
 // Entry-cache refresh (only when the next sweep reads the cache): for every
@@ -1569,11 +1643,11 @@ __global__ __launch_bounds__(256) void k_hub_cache_refresh(MoveArgs a, HubArgs h
 
 hipError_t launch_pairs_changed(int32_t m, int32_t nonhub, const int32_t* verts, const int32_t* off,
                                 const int32_t* comm, const int32_t* sigma, int2* cs, uint8_t* chg, int4* list,
-                                int32_t* cnt, int mode, SweepCtl* ctl, hipStream_t s)
+                                int32_t* cnt, int mode, const SweepEnd& end, hipStream_t s)
 {
     if (m <= 0) return hipSuccess;
-    k_pairs_changed<<<grid_for(m, 256, 8192), 256, 0, s>>>(m, nonhub, verts, off, comm, sigma, cs, chg, list, cnt,
-                                                           mode, ctl);
+    k_pairs_changed<<<grid_for(m, 256, COMMIT_GRID), 256, 0, s>>>(m, nonhub, verts, off, comm, sigma, cs, chg, list,
+                                                                  cnt, mode, end);
     return hipGetLastError();
 }
 hipError_t launch_cache_refresh(int32_t m, const int4* list, const int32_t* cnt, const int32_t* rev, int2* ce,
@@ -1608,25 +1682,25 @@ hipError_t launch_hub_mark(const MoveArgs& a, const HubArgs& h, int32_t* mark, h
 }
 
 hipError_t launch_pairs(int32_t n, const int32_t* verts, const int32_t* comm, const int32_t* sigma, int2* cs,
-                        const SweepCtl* ctl, hipStream_t s)
+                        const SweepEnd* end, hipStream_t s)
 {
-    if (n <= 0) return hipSuccess;
-    k_pairs<<<LV_GRID(n)>>>(n, verts, comm, sigma, cs, ctl);
+    if (end) {  // a level without entries still ends its sweep
+        k_pairs<true><<<grid_for(n, 256, COMMIT_GRID), 256, 0, s>>>(n, verts, comm, sigma, cs, *end);
+    } else if (n > 0) {
+        k_pairs<false><<<LV_GRID(n)>>>(n, verts, comm, sigma, cs, SweepEnd{});
+    }
     return hipGetLastError();
 }
-hipError_t launch_ctl_init(SweepCtl* ctl, int32_t G, const int32_t* gactive, int32_t* gdone, int32_t* gsweeps,
-                           uint32_t* gmoves, int32_t max_sweeps, hipStream_t s)
+hipError_t launch_ctl_init(SweepCtl* ctl, SweepCounters* ctr, int32_t G, const int32_t* gactive, int32_t* gdone,
+                           int32_t* gsweeps, uint32_t* gmoves, int32_t max_sweeps, hipStream_t s)
 {
-    k_ctl_init<<<grid_for((int64_t)G * max_sweeps + 1, 256, 4096), 256, 0, s>>>(ctl, G, gactive, gdone, gsweeps,
+    k_ctl_init<<<grid_for((int64_t)G * max_sweeps + 1, 256, 4096), 256, 0, s>>>(ctl, ctr, G, gactive, gdone, gsweeps,
                                                                              gmoves, max_sweeps);
     return hipGetLastError();
 }
-hipError_t launch_sweep_end(SweepCtl* ctl, int32_t G, int32_t* gdone, int32_t* gsweeps, const uint32_t* gmoves,
-                            int32_t max_sweeps, int64_t theta, int32_t consecutive, int64_t ec_read_max,
-                            int64_t ec_fill_max, hipStream_t s)
+hipError_t launch_sweep_end(const SweepEnd& end, hipStream_t s)
 {
-    k_sweep_end<<<1, 256, 0, s>>>(ctl, G, gdone, gsweeps, gmoves, max_sweeps, theta, consecutive, ec_read_max,
-                                  ec_fill_max);
+    k_sweep_end<<<1, 256, 0, s>>>(end);
     return hipGetLastError();
 }
 
@@ -1786,11 +1860,11 @@ hipError_t launch_hub_sweep(bool singleton, const MoveArgs& a, const HubArgs& h,
 }
 
 hipError_t launch_apply(const int32_t* verts, const int32_t* dec, int32_t m, const int32_t* k, const int32_t* gid,
-                        int32_t* comm, int32_t* sigma, const SweepCtl* ctl, uint32_t* gmoves, int32_t max_sweeps,
-                        hipStream_t s)
+                        int32_t* comm, int32_t* sigma, const SweepCtl* ctl, SweepCounters* ctr, uint32_t* gmoves,
+                        int32_t max_sweeps, hipStream_t s)
 {
     if (m <= 0) return hipSuccess;
-    k_apply<<<grid_for(m, 256, 2048), 256, 0, s>>>(verts, dec, m, k, gid, comm, sigma, ctl, gmoves, max_sweeps);
+    k_apply<<<grid_for(m, 256, 2048), 256, 0, s>>>(verts, dec, m, k, gid, comm, sigma, ctl, ctr, gmoves, max_sweeps);
     return hipGetLastError();
 }
 hipError_t launch_volumes(const int32_t* verts, int32_t m, const int32_t* k, const int32_t* comm, int32_t* sigma,
