@@ -341,6 +341,7 @@ struct Tune {
     int32_t fused;      // 1: later sweeps of the classes below the hub class in one persistent launch
     int32_t table_pct;  // later sweeps' LDS tables: about L * table_pct / 100 + 1 slots for L entries
     int32_t cache_read_pct;  // entry cache: read it after a commit that changed at most this % of the pairs
+    bool cache_forced;       // cache_pct was given: the cache is used on small levels too
     int32_t cache_fill_pct;  // ... fill it during a sweep after a commit that changed at most this %
 };
 
@@ -357,6 +358,7 @@ Tune make_tune(const lv_tuning* t)
     u.sc_chunk = 2048;
     u.agg_sort = 0;
     u.cache_read_pct = 10;
+    u.cache_forced = false;
     u.fused = 0;
     u.table_pct = 300;
     if (t) {
@@ -382,7 +384,10 @@ Tune make_tune(const lv_tuning* t)
         if (t->hub_chunk > 0) u.sc_chunk = t->hub_chunk <= 1024 ? 1024 : t->hub_chunk <= 2048 ? 2048 : 4096;
         if (t->order_min > 0) u.order_min = t->order_min;
         u.agg_sort = t->agg_sort == 1 ? 1 : 0;
-        if (t->cache_pct > 0) u.cache_read_pct = std::min(100, t->cache_pct);
+        if (t->cache_pct > 0) {
+            u.cache_read_pct = std::min(100, t->cache_pct);
+            u.cache_forced = true;
+        }
         u.fused = t->fused == 1 ? 1 : 0;
         if (t->table_pct > 0) u.table_pct = std::min(400, std::max(100, t->table_pct));
     }
@@ -688,6 +693,37 @@ lv_status plan_hubs(lv_graph* g, const LevelGraph& G, const int32_t* hub_verts, 
 }
 
 
+// Levels of fewer entries run their sweeps as two launches each (see
+// run_sweeps).  There the number of launches is the cost: 20 LPA sweeps of a
+// 10 K-vertex R-MAT graph took 1.10 ms with a launch per class and take 0.42 ms
+// so.  On large levels the 1024-thread workgroups of the merged kernel wait for
+// their slowest group and hide less latency: 8.1 ms for 20 sweeps of a
+// 30.5 M-entry level against 6.1 ms with a launch per class, and 130 against
+// 81 ms at 509 M entries.  Between 4 M and 16 M entries both are alike.
+constexpr int64_t SMALL_NNZ = (int64_t)1 << 22;
+constexpr int32_t SMALL_LAG = 3;  // sweeps launched ahead of the last one known to be done
+
+bool mail_done(const SweepMail* m) { return __atomic_load_n(&m->done, __ATOMIC_ACQUIRE) != 0; }
+
+// Wait until `sweeps` sweeps are done or the level has ended, as the device
+// posts it in pinned memory.  Gives up with an error when the stream has
+// failed, or has drained without posting.
+lv_status await_sweeps(hipStream_t s, const SweepMail* m, int32_t sweeps)
+{
+    for (uint64_t spin = 1;; ++spin) {
+        if (mail_done(m) || __atomic_load_n(&m->sweeps, __ATOMIC_ACQUIRE) >= sweeps) return LV_OK;
+        if (spin % 1024 == 0) {
+            const hipError_t e = hipStreamQuery(s);
+            if (e == hipErrorNotReady) continue;
+            if (e != hipSuccess) { set_error("sweeps", e); return from_hip(e); }
+            if (mail_done(m) || __atomic_load_n(&m->sweeps, __ATOMIC_ACQUIRE) >= sweeps) return LV_OK;
+            set_error_msg("the sweeps ended without reporting");
+            return LV_E_HIP;
+        }
+        __builtin_ia32_pause();
+    }
+}
+
 // Synchronous local-moving sweeps of one level (Algorithm 2; Algorithm 1 in
 // LPA mode) for every graph of G.  gactive (device, may be null) marks the
 // graphs that take part.  On return ws.comm holds the labels and ws.sigma the
@@ -748,8 +784,15 @@ lv_status run_sweeps(lv_graph* g, const LevelGraph& G, int mode, const Params& p
     const bool async = (p.flags & LV_ASYNC) != 0;
     // Entry cache: on the handle's input graph (its reverse-entry map
     // exists), for full synchronous sweeps.  The device decides per sweep
-    // whether to read, fill or bypass it (k_sweep_end).
-    const bool use_ec = G.rev && G.nnz > 0 && active > 0 && !(p.flags & (LV_NO_CACHE | LV_PRUNE | LV_ASYNC));
+    // whether to read, fill or bypass it (k_sweep_end).  Below SMALL_NNZ
+    // entries the gathered pairs stay in an XCD's 4 MiB L2 and the cache only
+    // adds launches, so it is left to an explicit cache_pct.
+    const bool use_ec = G.rev && G.nnz > 0 && active > 0 && !(p.flags & (LV_NO_CACHE | LV_PRUNE | LV_ASYNC)) &&
+                        (G.nnz >= SMALL_NNZ || p.tune.cache_forced);
+    // Small levels: two launches a sweep (k_move_merged and the pair refresh),
+    // plus the partition kernels where there are hubs.
+    const bool small = G.nnz < SMALL_NNZ && !use_ec && !timing && !async && !(p.flags & LV_PRUNE) &&
+                       p.tune.fused == 0 && (hubs.nhubs == 0 || hubs.args.bucketed);
     if (use_ec) {
         HIP_TRY(ws.ce.ensure(sizeof(int2) * (size_t)G.nnz));
         HIP_TRY(ws.chg.ensure((size_t)std::max(active, 1)));
@@ -760,21 +803,22 @@ lv_status run_sweeps(lv_graph* g, const LevelGraph& G, int mode, const Params& p
     const int64_t ec_read_max = use_ec ? G.nnz * p.tune.cache_read_pct / 100 : -1;
     const int64_t ec_fill_max = use_ec ? G.nnz * p.tune.cache_fill_pct / 100 : -1;
     const int32_t nonhub = start[CLS_HUB] - start[CLS_L4];  // listed vertices below the hub class
-    // the fused kernel's work items: blocks of rows, longest rows first
+    // the fused and merged kernels' work items: blocks of rows, longest rows first
     FusedMap fmap{};
     const bool fused = p.tune.fused != 0 && !async;
-    if (fused) {
-        static const int32_t rows_per_item[NUM_CLS] = {0, 256, 128, 64, 32, 16, 8, 4, 2, 2, 1, 0};
+    if (fused || small) {
         int32_t items = 0;
-        for (int c = CLS_HUB - 1; c >= CLS_L4; --c) {
+        for (int c = fused ? CLS_HUB - 1 : CLS_HUB; c >= CLS_L4; --c) {
             const int32_t cnt = start[c + 1] - start[c];
             if (cnt <= 0) continue;
+            // the fused kernel gives the 4-entry class 4 lanes a row
+            const int32_t rows_per_item = fused && c == CLS_L4 ? merged_rows(c) / 4 : merged_rows(c);
             const int q = fmap.nclass++;
             fmap.cls[q] = c;
             fmap.item_first[q] = items;
             fmap.row_first[q] = start[c] - start[CLS_L4];
             fmap.row_end[q] = start[c + 1] - start[CLS_L4];
-            items += (cnt + rows_per_item[c] - 1) / rows_per_item[c];
+            items += (cnt + rows_per_item - 1) / rows_per_item;
         }
         fmap.item_first[fmap.nclass] = items;
     }
@@ -834,8 +878,9 @@ lv_status run_sweeps(lv_graph* g, const LevelGraph& G, int mode, const Params& p
     const int64_t theta = mode == MODE_LPA ? p.lpa_threshold : 0;
     // synchronous sweeps alternate direction, so a level ends after two
     // quiet sweeps; an asynchronous level ends after one (Alg. 2's test)
-    const SweepEnd end{ctl, ws.ctr.as<SweepCounters>(), G.G, ws.gdone.as<int32_t>(), ws.gsweeps.as<int32_t>(),
-                       ws.gmoves.as<uint32_t>(), S, theta, async ? 1 : 2, ec_read_max, ec_fill_max};
+    SweepEnd end{ctl, ws.ctr.as<SweepCounters>(), G.G, ws.gdone.as<int32_t>(), ws.gsweeps.as<int32_t>(),
+                 ws.gmoves.as<uint32_t>(), S, theta, async ? 1 : 2, ec_read_max, ec_fill_max,
+                 nullptr, nullptr, nullptr, nullptr};
 
     Timer tm;
     tm.on = timing;
@@ -932,16 +977,60 @@ lv_status run_sweeps(lv_graph* g, const LevelGraph& G, int mode, const Params& p
                 if (e) (void)hipEventDestroy(e);
         }
     } held{s};
-    const bool poll = use_graph && S > 2 && G.nnz >= ((int64_t)1 << 20);
+    const bool poll = use_graph && !small && S > 2;
     int32_t* h_flag = (int32_t*)((char*)g->pinned + poll_off);
     if (poll) {
         *h_flag = 0;
         for (hipEvent_t& e : held.ev) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     }
+    // per-graph move and sweep counts and the control block, in pinned memory
+    uint32_t* h_moves = (uint32_t*)g->pinned;
+    int32_t* h_sweeps = (int32_t*)(h_moves + (size_t)G.G * S);
+    SweepCtl* h_ctl = (SweepCtl*)(((uintptr_t)(h_sweeps + G.G) + 15) & ~(uintptr_t)15);
     Timer ph;
     ph.s = s;
     hipEvent_t p0{}, p1{};
-    if (use_graph) {
+    if (small) {
+        // Sweeps are launched directly, at most SMALL_LAG ahead of the device,
+        // which posts its progress and then the results in pinned memory.
+        SweepMail* mail = (SweepMail*)h_flag;
+        mail->sweeps = mail->done = 0;
+        void* dp = nullptr;
+        HIP_TRY(hipHostGetDevicePointer(&dp, g->pinned, 0));
+        const auto on_device = [&](void* h) { return (char*)dp + ((char*)h - (char*)g->pinned); };
+        end.mail = (SweepMail*)on_device(mail);
+        end.h_moves = (uint32_t*)on_device(h_moves);
+        end.h_sweeps = (int32_t*)on_device(h_sweeps);
+        end.h_ctl = (SweepCtl*)on_device(h_ctl);
+        MoveArgs m = a;
+        m.rows = ws.rows.as<int4>();
+        m.dec = dec_all + start[CLS_L4];
+        m.verts = act_verts;
+        m.nverts = active;
+        m.commit_comm = ws.comm.as<int32_t>();
+        m.commit_sigma = mode == MODE_LPA ? nullptr : ws.sigma.as<int32_t>();
+        m.ctr = ws.ctr.as<SweepCounters>();
+        HIP_TRY(ph.mark(&p0));
+        for (int32_t sw = 1; sw <= S; ++sw) {
+            if (sw > SMALL_LAG) {
+                LV_TRY(await_sweeps(s, mail, sw - SMALL_LAG));
+                if (mail_done(mail)) break;
+            }
+            if (hubs.nhubs > 0) {  // decided before any label or volume changes
+                a.verts = vert_sorted + start[CLS_HUB];
+                a.rows = nullptr;
+                a.dec = dec_all + start[CLS_HUB];
+                a.nverts = hubs.nhubs;
+                HIP_TRY(launch_hub_scatter(a, hubs.args, s));
+                HIP_TRY(launch_hub_sweep(false, a, hubs.args, s));
+            }
+            HIP_TRY(launch_move_merged(m, fmap, s));
+            HIP_TRY(launch_pairs(active, act_verts, ws.comm.as<int32_t>(), ws.sigma.as<int32_t>(), ws.cs.as<int2>(),
+                                 &end, s));
+        }
+        HIP_TRY(ph.mark(&p1));
+        LV_TRY(await_sweeps(s, mail, INT32_MAX));
+    } else if (use_graph) {
         // The first sweep (every community a single vertex) is launched
         // directly; while it runs, a later sweep is captured once and then
         // replayed up to max_sweeps - 1 times: the kernels read the sweep
@@ -994,13 +1083,13 @@ lv_status run_sweeps(lv_graph* g, const LevelGraph& G, int mode, const Params& p
         HIP_TRY(launch_fill_i32(ws.sigma.as<int32_t>(), 0, n, s));
         HIP_TRY(launch_volumes(act_verts, active, G.k, ws.comm.as<int32_t>(), ws.sigma.as<int32_t>(), s));
     }
-    // per-graph sweep and move counts (one host round trip per level)
-    uint32_t* h_moves = (uint32_t*)g->pinned;
-    int32_t* h_sweeps = (int32_t*)(h_moves + (size_t)G.G * S);
-    SweepCtl* h_ctl = (SweepCtl*)(((uintptr_t)(h_sweeps + G.G) + 15) & ~(uintptr_t)15);
-    HIP_TRY(hipMemcpyAsync(h_moves, ws.gmoves.p, sizeof(uint32_t) * (size_t)G.G * S, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(h_sweeps, ws.gsweeps.p, sizeof(int32_t) * (size_t)G.G, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(h_ctl, ws.ctl.p, sizeof(SweepCtl), hipMemcpyDeviceToHost, s));
+    // one host round trip per level (a small level's results are here already;
+    // its phase time still wants the last event)
+    if (!small) {
+        HIP_TRY(hipMemcpyAsync(h_moves, ws.gmoves.p, sizeof(uint32_t) * (size_t)G.G * S, hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipMemcpyAsync(h_sweeps, ws.gsweeps.p, sizeof(int32_t) * (size_t)G.G, hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipMemcpyAsync(h_ctl, ws.ctl.p, sizeof(SweepCtl), hipMemcpyDeviceToHost, s));
+    }
     HIP_TRY(hipStreamSynchronize(s));
     // every fallback scan of this level has run: a table its hubs used is
     // clean again (a level without hubs leaves the flag as it was)

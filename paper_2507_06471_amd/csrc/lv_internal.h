@@ -77,6 +77,14 @@ struct SweepCounters {
     alignas(128) uint32_t ways_done;
 };
 
+// How far a level has come, in pinned host memory: the host launches sweeps a
+// few ahead and neither waits for the stream nor copies to learn that the
+// level has ended.
+struct SweepMail {
+    int32_t sweeps;  // finished sweeps
+    int32_t done;    // every graph has stopped; the results are in host memory
+};
+
 // What ends a sweep (k_sweep_end's arguments), run by the last workgroup of
 // the pair refresh.
 struct SweepEnd {
@@ -91,6 +99,13 @@ struct SweepEnd {
     int32_t consecutive;
     int64_t ec_read_max;    // the next sweep reads the entry cache if it was filled and at most this
     int64_t ec_fill_max;    // many entries changed, else fills it if at most ec_fill_max did (-1: no cache)
+    // pinned host memory (null: none): the number of finished sweeps after
+    // each one, and, once every graph has stopped, the level's results before
+    // `done` is set
+    SweepMail* mail;
+    uint32_t* h_moves;      // [G * max_sweeps]
+    int32_t* h_sweeps;      // [G]
+    SweepCtl* h_ctl;
 };
 
 // Arguments shared by every move kernel.
@@ -130,6 +145,12 @@ struct MoveArgs {
     // the reverse-entry map).
     int2* ce;
     int32_t table_pct;      // later sweeps' LDS table: about L * table_pct / 100 + 1 slots for L entries
+    // Small levels (k_move_merged<true>): movers take their community at once
+    // (null otherwise).  The move kernels read only cs, the last sweep's
+    // state, so labels and volumes may change under them.
+    int32_t* commit_comm;
+    int32_t* commit_sigma;  // null for LPA (its scores never read volumes)
+    SweepCounters* ctr;
 };
 
 // One segment of a packed CSR rebuild (see launch_repack).
@@ -291,6 +312,12 @@ struct FusedMap {
     int32_t row_end[NUM_CLS];
 };
 hipError_t launch_move_fused(const MoveArgs& a, const FusedMap& fm, SweepCtl* ctl, hipStream_t s);
+// A whole sweep of a small level but for the pair refresh: every class of fm
+// in one launch (k_move_merged), movers committed at once.  fm's items are
+// blocks of merged_rows(cls) rows; CLS_HUB rows have been decided already
+// (a.dec) and are only committed.
+int32_t merged_rows(int cls);
+hipError_t launch_move_merged(const MoveArgs& a, const FusedMap& fm, hipStream_t s);
 hipError_t launch_hub_clear(int32_t* table, int64_t slots, hipStream_t s);
 hipError_t launch_chunk_list(const int32_t* first, int32_t nhubs, int32_t total, const int32_t* base,
                              const int32_t* len, int32_t chunk, int32_t* o_hub, int32_t* o_beg, int32_t* o_end,

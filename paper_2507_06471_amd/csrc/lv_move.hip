@@ -193,19 +193,23 @@ __device__ __forceinline__ bool decide_apply(const MoveArgs& a, int64_t pos, int
     return mover;
 }
 
-// Decision of vertex-list slot `pos`: the best community if it beats staying
-// and lies in the sweep's direction, else -1.
+// Whether a vertex of community A moves to its best community: it must beat
+// staying and lie in the sweep's direction.
+__device__ __forceinline__ bool decide(const MoveArgs& a, int32_t A, int32_t sA, int64_t ki, int64_t M, int64_t best_s,
+                                       int32_t best_c, int32_t w_own)
+{
+    if (best_c == INT32_MAX) return false;
+    const bool louvain = a.mode == MODE_LOUVAIN;
+    const int64_t stay = louvain ? louvain_score(M, w_own, ki, (int64_t)sA - ki) : (int64_t)w_own;
+    const bool dir_ok = sweep_dir(a.ctl) == DIR_DOWN ? best_c < A : best_c > A;
+    return best_s > stay && dir_ok;
+}
+
+// Decision of vertex-list slot `pos`: the community it moves to, else -1.
 __device__ __forceinline__ void decide_store(const MoveArgs& a, int64_t pos, int32_t A, int32_t sA, int64_t ki,
                                              int64_t M, int64_t best_s, int32_t best_c, int32_t w_own)
 {
-    bool mover = false;
-    if (best_c != INT32_MAX) {
-        const bool louvain = a.mode == MODE_LOUVAIN;
-        const int64_t stay = louvain ? louvain_score(M, w_own, ki, (int64_t)sA - ki) : (int64_t)w_own;
-        const bool dir_ok = sweep_dir(a.ctl) == DIR_DOWN ? best_c < A : best_c > A;
-        mover = best_s > stay && dir_ok;
-    }
-    a.dec[pos] = mover ? best_c : -1;
+    a.dec[pos] = decide(a, A, sA, ki, M, best_s, best_c, w_own) ? best_c : -1;
 }
 
 // Entry cache access: 8-byte streaming load / store of entry e's pair.
@@ -529,6 +533,103 @@ __global__ __launch_bounds__(BS) void k_move(MoveArgs a)
     if constexpr (ASYNC) block_flush_sums<BS, uint32_t>(a.gmoves, moved ? move_slot(a, i) : -1, moved ? 1u : 0u);
 }
 
+// ------------------------------------------------------------------ commit table
+// Apply the decisions of the m listed vertices: labels and community
+// volumes (LPA's modularity reads the volumes too).  Every mover adds its
+// volume change for the community it leaves and the one it joins into the
+// workgroup's LDS table (integer sums, so order is irrelevant; see
+// peeled_apply); the table is added into the volumes once at the end, so a
+// community that many movers leave or join costs one global atomic per
+// workgroup.  A change that finds no table slot within APPLY_PROBE probes,
+// or is for a community not yet in the table once it holds APPLY_FILL
+// communities (a workgroup whose movers touch many communities gains nothing
+// from more), is added globally at once.  The movers of graph g in this sweep
+// are counted in gmoves[g * max_sweeps + sweep].
+constexpr int APPLY_SLOTS = 4096;
+constexpr int APPLY_PROBE = 16;
+constexpr int APPLY_FILL = APPLY_SLOTS * 3 / 4;
+
+__device__ __forceinline__ void apply_add(int32_t* key, int32_t* val, int32_t* fill, int32_t* sigma, int32_t C,
+                                          int32_t d)
+{
+    // a community already in the table always adds there; a new one takes
+    // a slot only while the table holds fewer than APPLY_FILL communities
+    constexpr uint32_t AMASK = (uint32_t)(APPLY_SLOTS - 1);
+    Probe pr = probe_start<false>(C, AMASK);
+    for (int p = 0; p < APPLY_PROBE; ++p) {
+        const int32_t k = *(volatile int32_t*)&key[pr.h];
+        if (k == C) { atomicAdd(&val[pr.h], d); return; }
+        if (k == EMPTY_KEY) {
+            if (*(volatile int32_t*)fill >= APPLY_FILL) break;
+            const int32_t prev = atomicCAS(&key[pr.h], EMPTY_KEY, C);
+            if (prev == EMPTY_KEY) atomicAdd(fill, 1);
+            if (prev == EMPTY_KEY || prev == C) { atomicAdd(&val[pr.h], d); return; }
+        }
+        probe_next<false>(pr, AMASK);
+    }
+    atomicAdd(&sigma[C], d);
+}
+
+// Add d to community C for every valid lane: the lanes that share the first
+// valid lane's community are summed into one add (movers crowding into one
+// large community), every other lane adds on its own (the LDS atomics sort
+// out any further collisions).  Reached by all lanes of the wavefront.
+__device__ __forceinline__ void peeled_apply(int32_t* key, int32_t* val, int32_t* fill, int32_t* sigma, int32_t C,
+                                             int32_t d, bool valid)
+{
+    const uint64_t any = __ballot(valid);
+    if (!any) return;
+    const int leader = __ffsll((unsigned long long)any) - 1;
+    const int32_t lc = __shfl(C, leader);
+    const bool mine = valid && C == lc;
+    int32_t c = mine ? d : 0;
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) c += __shfl_xor(c, m);
+    if ((int)lane_id() == leader && c) apply_add(key, val, fill, sigma, lc, c);
+    if (valid && !mine && d) apply_add(key, val, fill, sigma, C, d);
+}
+
+// Commit within a move kernel (small levels): each thread's mover (vertex i
+// from community A to C) takes its label at once, the volumes follow, and the
+// workgroup's movers are counted.  A few movers add to the volumes directly;
+// many are summed per community in the workgroup's tables, free by now (tab:
+// at least APPLY_SLOTS 8-byte slots), so that a community that everyone joins
+// costs one atomic per workgroup.  Every thread of the workgroup calls it.
+constexpr int COMMIT_DIRECT = 48;
+template <int BS>
+__device__ __forceinline__ void commit_movers(const MoveArgs& a, unsigned long long* tab, bool mover, int32_t i,
+                                              int32_t A, int32_t C, int32_t ki)
+{
+    __shared__ int32_t t_fill;
+    const int32_t n = __syncthreads_count(mover);  // also: every group is done with its table
+    if (n == 0) return;
+    if (mover) a.commit_comm[i] = C;
+    if (a.gid) {
+        wave_grouped_add<uint32_t, uint32_t>(a.gmoves, mover ? move_slot(a, i) : 0, 1u, mover);
+    } else if (threadIdx.x == 0) {
+        atomicAdd(&a.ctr->way[blockIdx.x % CTR_WAYS].moves, (uint32_t)n);
+    }
+    int32_t* sigma = a.commit_sigma;
+    if (!sigma) return;
+    if (n <= COMMIT_DIRECT) {
+        if (mover) {
+            atomicAdd(&sigma[A], -ki);
+            atomicAdd(&sigma[C], ki);
+        }
+        return;
+    }
+    int32_t* key = (int32_t*)tab;
+    int32_t* val = key + APPLY_SLOTS;
+    if (threadIdx.x == 0) t_fill = 0;
+    for (int t = threadIdx.x; t < APPLY_SLOTS; t += BS) { key[t] = EMPTY_KEY; val[t] = 0; }
+    __syncthreads();
+    peeled_apply(key, val, &t_fill, sigma, C, ki, mover);
+    peeled_apply(key, val, &t_fill, sigma, A, -ki, mover);
+    __syncthreads();
+    for (int t = threadIdx.x; t < APPLY_SLOTS; t += BS)
+        if (key[t] != EMPTY_KEY && val[t] != 0) atomicAdd(&sigma[key[t]], val[t]);
+}
+
 // Later synchronous sweeps: one group of G lanes per vertex (a block of BS
 // threads holds BS/G groups; group g takes listed row vi_first + g if it is
 // below vi_end), an LDS table of up to SLOTS packed slots per group at
@@ -536,7 +637,8 @@ __global__ __launch_bounds__(BS) void k_move(MoveArgs a)
 // the volume that came with the entry's pair (no scan of the table, no volume
 // array).  rs/rc/rw: BS/64 entries for the reduction across wavefronts.
 // Every thread of the block calls it with the same arguments.
-template <int CLS, int BS, int G, int SLOTS>
+// COMMIT: movers are committed here (commit_movers) instead of recorded.
+template <int CLS, int BS, int G, int SLOTS, bool COMMIT = false>
 __device__ __forceinline__ void claim_rows(const MoveArgs& a, int ecm, int64_t vi_first, int64_t vi_end,
                                            unsigned long long* s_tab, int64_t* rs, int32_t* rc, int32_t* rw)
 {
@@ -624,7 +726,10 @@ __device__ __forceinline__ void claim_rows(const MoveArgs& a, int ecm, int64_t v
             }
         }
     }
-    if (has && lane == 0) {
+    if constexpr (COMMIT) {
+        const bool mover = lane == 0 && live && decide(a, A, self.y, ki, M, best_s, best_c, w_own);
+        commit_movers<BS>(a, s_tab, mover, i, A, best_c, (int32_t)ki);
+    } else if (has && lane == 0) {
         if (!live) a.dec[vi] = -1;
         else decide_store(a, vi, A, self.y, ki, M, best_s, best_c, w_own);
     }
@@ -703,31 +808,15 @@ __global__ __launch_bounds__(FUSED_BS) void k_move_fused(MoveArgs a, FusedMap fm
 // lane per row and no table.  The lane holds its row's pairs in
 // registers; entry u sums the weights of every entry of the row with its
 // community, and the first entry of each community scores it.
-constexpr int REG_BS = 256;
-template <int CLS>
-__global__ __launch_bounds__(REG_BS) void k_move_reg(MoveArgs a)
+template <int ME>
+__device__ __forceinline__ void reg_best(const MoveArgs& a, int ecm, int32_t i, int32_t beg, int32_t end, int32_t A,
+                                         int64_t ki, int64_t M, int64_t& best_s, int32_t& best_c, int32_t& w_own)
 {
-    constexpr int ME = CLS_CAP[CLS];
     static_assert(ME >= 1 && ME <= 4, "rows held in registers");
-    if (a.ctl->all_done) return;
-    const int64_t vi = (int64_t)blockIdx.x * REG_BS + threadIdx.x;
-    if (vi >= a.nverts) return;
-    const int4 row = a.rows[vi];
-    const int32_t i = row.x;
-    if (vertex_frozen(a, i) || vertex_skipped(a, i)) {
-        a.dec[vi] = -1;
-        return;
-    }
-    const int2 self = a.cs[i];
-    const int32_t A = self.x;
-    const int64_t ki = row.w;
-    const int64_t M = vertex_M(a, i);
     int2 cc[ME];
     int32_t ww[ME];
-    load_pairs<1, ME>(a, i, row.y, row.z, entry_mode(a), cc, ww);
+    load_pairs<1, ME>(a, i, beg, end, ecm, cc, ww);
     const bool louvain = a.mode == MODE_LOUVAIN;
-    int64_t best_s = INT64_MIN;
-    int32_t best_c = INT32_MAX, w_own = 0;
 #pragma unroll
     for (int u = 0; u < ME; ++u) {
         const int32_t C = cc[u].x;
@@ -743,7 +832,90 @@ __global__ __launch_bounds__(REG_BS) void k_move_reg(MoveArgs a)
         const int64_t sc = louvain ? louvain_score(M, W, ki, cc[u].y) : (int64_t)W;
         if (better(sc, C, best_s, best_c)) { best_s = sc; best_c = C; }
     }
-    decide_store(a, vi, A, self.y, ki, M, best_s, best_c, w_own);
+}
+
+constexpr int REG_BS = 256;
+template <int CLS>
+__global__ __launch_bounds__(REG_BS) void k_move_reg(MoveArgs a)
+{
+    if (a.ctl->all_done) return;
+    const int64_t vi = (int64_t)blockIdx.x * REG_BS + threadIdx.x;
+    if (vi >= a.nverts) return;
+    const int4 row = a.rows[vi];
+    const int32_t i = row.x;
+    if (vertex_frozen(a, i) || vertex_skipped(a, i)) {
+        a.dec[vi] = -1;
+        return;
+    }
+    const int2 self = a.cs[i];
+    const int64_t M = vertex_M(a, i);
+    int64_t best_s = INT64_MIN;
+    int32_t best_c = INT32_MAX, w_own = 0;
+    reg_best<CLS_CAP[CLS]>(a, entry_mode(a), i, row.y, row.z, self.x, row.w, M, best_s, best_c, w_own);
+    decide_store(a, vi, self.x, self.y, row.w, M, best_s, best_c, w_own);
+}
+
+// One sweep of a small level (synchronous, no entry cache): every class in one
+// launch, and its movers committed in place, so that a sweep is this launch
+// and the pair refresh.  A small level's kernels are each far shorter than
+// the 4-5 us that a launch takes with its gap, so their number is what a sweep
+// costs: a 34 K-entry level took 12 launches and 45 us a sweep.  Workgroups
+// have 1024 threads, laid out as the fused kernel lays out its items, with the
+// largest class's table (79 KiB, two workgroups a CU); the pad that small
+// classes do not use costs nothing where the chip is not full.  Every sweep,
+// the first included, goes through the tables.  Rows of hubs are decided by
+// the partition kernels before this launch and committed here.
+constexpr int MERGED_BS = 1024;
+__global__ __launch_bounds__(MERGED_BS) void k_move_merged(MoveArgs a, FusedMap fm)
+{
+    __shared__ __align__(16) unsigned long long s_tab[FUSED_SLOTS];
+    __shared__ int64_t rs[MERGED_BS / WAVE];
+    __shared__ int32_t rc[MERGED_BS / WAVE], rw[MERGED_BS / WAVE];
+    static_assert(APPLY_SLOTS <= FUSED_SLOTS, "the commit's table lies in the claim tables");
+    if (a.ctl->all_done) return;
+    const int32_t b = (int32_t)blockIdx.x;
+    int q = 0;
+    while (q + 1 < fm.nclass && fm.item_first[q + 1] <= b) ++q;
+    const int64_t k = b - fm.item_first[q];
+    const int64_t r0 = fm.row_first[q], r1 = fm.row_end[q];
+#define LV_MERGED_CASE(C, G, SL)                                                                                   \
+    case C:                                                                                                        \
+        claim_rows<C, MERGED_BS, G, SL, true>(a, EC_GATHER, r0 + k * (MERGED_BS / G), r1, s_tab, rs, rc, rw);      \
+        break;
+    switch (fm.cls[q]) {
+        case CLS_L4:
+        case CLS_HUB: {  // one lane per row: its best community found here, or decided already
+            const int64_t vi = r0 + k * MERGED_BS + threadIdx.x;
+            const bool has = vi < r1;
+            const int4 row = has ? a.rows[vi] : make_int4(0, 0, 0, 0);
+            const bool live = has && !vertex_frozen(a, row.x);
+            int64_t best_s = INT64_MIN;
+            int32_t best_c = INT32_MAX, w_own = 0;
+            const int2 self = live ? a.cs[row.x] : make_int2(0, 0);
+            bool mover = false;
+            if (fm.cls[q] == CLS_HUB) {
+                best_c = live ? a.dec[vi] : -1;
+                mover = best_c >= 0;
+            } else if (live) {
+                const int64_t M = vertex_M(a, row.x);
+                reg_best<CLS_CAP[CLS_L4]>(a, EC_GATHER, row.x, row.y, row.z, self.x, row.w, M, best_s, best_c, w_own);
+                mover = decide(a, self.x, self.y, row.w, M, best_s, best_c, w_own);
+            }
+            commit_movers<MERGED_BS>(a, s_tab, mover, row.x, self.x, best_c, row.w);
+            break;
+        }
+        LV_MERGED_CASE(CLS_L8, 4, L8_SLOTS)
+        LV_MERGED_CASE(CLS_L32, 8, L32_SLOTS)
+        LV_MERGED_CASE(CLS_L128, 32, L128_SLOTS)
+        LV_MERGED_CASE(CLS_L256, 64, L256_SLOTS)
+        LV_MERGED_CASE(CLS_L512, 128, L512_SLOTS)
+        LV_MERGED_CASE(CLS_L1K, 256, L1K_SLOTS)
+        LV_MERGED_CASE(CLS_L2K, 512, L2K_SLOTS)
+        LV_MERGED_CASE(CLS_L3K, 512, L3K_SLOTS)
+        LV_MERGED_CASE(CLS_L8K, 1024, L8K_SLOTS)
+        default: break;
+    }
+#undef LV_MERGED_CASE
 }
 
 template <int CLS, int BS, int G, int SLOTS>
@@ -1216,61 +1388,6 @@ __global__ __launch_bounds__(256) void k_hub_mark(MoveArgs a, HubArgs h, int32_t
 }
 
 // ------------------------------------------------------------------ commit (K7)
-// Apply the decisions of the m listed vertices: labels and community
-// volumes (LPA's modularity reads the volumes too).  Every mover adds its
-// volume change for the community it leaves and the one it joins into the
-// workgroup's LDS table (integer sums, so order is irrelevant; see
-// peeled_apply); the table is added into the volumes once at the end, so a
-// community that many movers leave or join costs one global atomic per
-// workgroup.  A change that finds no table slot within APPLY_PROBE probes,
-// or is for a community not yet in the table once it holds APPLY_FILL
-// communities (a workgroup whose movers touch many communities gains nothing
-// from more), is added globally at once.  The movers of graph g in this sweep
-// are counted in gmoves[g * max_sweeps + sweep].
-constexpr int APPLY_SLOTS = 4096;
-constexpr int APPLY_PROBE = 16;
-constexpr int APPLY_FILL = APPLY_SLOTS * 3 / 4;
-
-__device__ __forceinline__ void apply_add(int32_t* key, int32_t* val, int32_t* fill, int32_t* sigma, int32_t C,
-                                          int32_t d)
-{
-    // a community already in the table always adds there; a new one takes
-    // a slot only while the table holds fewer than APPLY_FILL communities
-    constexpr uint32_t AMASK = (uint32_t)(APPLY_SLOTS - 1);
-    Probe pr = probe_start<false>(C, AMASK);
-    for (int p = 0; p < APPLY_PROBE; ++p) {
-        const int32_t k = *(volatile int32_t*)&key[pr.h];
-        if (k == C) { atomicAdd(&val[pr.h], d); return; }
-        if (k == EMPTY_KEY) {
-            if (*(volatile int32_t*)fill >= APPLY_FILL) break;
-            const int32_t prev = atomicCAS(&key[pr.h], EMPTY_KEY, C);
-            if (prev == EMPTY_KEY) atomicAdd(fill, 1);
-            if (prev == EMPTY_KEY || prev == C) { atomicAdd(&val[pr.h], d); return; }
-        }
-        probe_next<false>(pr, AMASK);
-    }
-    atomicAdd(&sigma[C], d);
-}
-
-// Add d to community C for every valid lane: the lanes that share the first
-// valid lane's community are summed into one add (movers crowding into one
-// large community), every other lane adds on its own (the LDS atomics sort
-// out any further collisions).  Reached by all lanes of the wavefront.
-__device__ __forceinline__ void peeled_apply(int32_t* key, int32_t* val, int32_t* fill, int32_t* sigma, int32_t C,
-                                             int32_t d, bool valid)
-{
-    const uint64_t any = __ballot(valid);
-    if (!any) return;
-    const int leader = __ffsll((unsigned long long)any) - 1;
-    const int32_t lc = __shfl(C, leader);
-    const bool mine = valid && C == lc;
-    int32_t c = mine ? d : 0;
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) c += __shfl_xor(c, m);
-    if ((int)lane_id() == leader && c) apply_add(key, val, fill, sigma, lc, c);
-    if (valid && !mine && d) apply_add(key, val, fill, sigma, C, d);
-}
-
 // Commit of one synchronous sweep: every mover takes its new community, and
 // (sigma not null) the community volumes follow.  LPA passes no volumes: its
 // scores never read them, and they are summed once from the final labels
@@ -1401,7 +1518,9 @@ __device__ __forceinline__ void end_sweep(const SweepEnd& p)
         if (stop) { p.gdone[g] = 1; p.gsweeps[g] = s; } else ++running;
     }
     running = block_sum<BS>(running, red);
+    __shared__ int32_t s_stop;
     if (threadIdx.x == 0) {
+        s_stop = running == 0;
         ctl->sweep = s;
         ctl->all_done = running == 0 ? 1 : 0;
         ctl->work_next = 0;
@@ -1418,6 +1537,19 @@ __device__ __forceinline__ void end_sweep(const SweepEnd& p)
                 ctl->refreshed += chg;
             }
         }
+    }
+    if (!p.mail) return;
+    __syncthreads();
+    if (s_stop) {
+        for (int64_t t = threadIdx.x; t < (int64_t)p.G * p.max_sweeps; t += BS) p.h_moves[t] = p.gmoves[t];
+        for (int32_t g = threadIdx.x; g < p.G; g += BS) p.h_sweeps[g] = p.gsweeps[g];
+        if (threadIdx.x == 0) *p.h_ctl = *ctl;
+        __threadfence_system();
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(&p.mail->sweeps, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        if (s_stop) __hip_atomic_store(&p.mail->done, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
@@ -1751,6 +1883,18 @@ hipError_t launch_move_fused(const MoveArgs& a, const FusedMap& fm, SweepCtl* ct
     // two workgroups fit a CU (LDS of the largest class's table)
     const int32_t items = fm.item_first[fm.nclass];
     k_move_fused<<<(unsigned)(items < 512 ? items : 512), FUSED_BS, 0, s>>>(a, fm, ctl);
+    return hipGetLastError();
+}
+
+int32_t merged_rows(int cls)
+{
+    constexpr int32_t G[NUM_CLS] = {1, 1, 4, 8, 32, 64, 128, 256, 512, 512, 1024, 1};  // lanes per row
+    return MERGED_BS / G[cls];
+}
+hipError_t launch_move_merged(const MoveArgs& a, const FusedMap& fm, hipStream_t s)
+{
+    if (fm.nclass <= 0 || fm.item_first[fm.nclass] <= 0) return hipSuccess;
+    k_move_merged<<<(unsigned)fm.item_first[fm.nclass], MERGED_BS, 0, s>>>(a, fm);
     return hipGetLastError();
 }
 
