@@ -122,7 +122,10 @@ __global__ __launch_bounds__(TILE_BS) void k_tile_keys(int32_t n, const int32_t*
     const int64_t total = (int64_t)n + nnz;
     const int64_t d0 = (int64_t)blockIdx.x * AG_T;
     const int64_t d1 = d0 + AG_T < total ? d0 + AG_T : total;
-    if (threadIdx.x < 2) s_x[threadIdx.x] = mp_rows(off, n, threadIdx.x ? d1 : d0);
+    if (threadIdx.x < 2 * WAVE) {
+        const int64_t x = mp_rows(off, n, threadIdx.x < WAVE ? d0 : d1);
+        if (lane_id() == 0) s_x[threadIdx.x / WAVE] = x;
+    }
     if (threadIdx.x == 0) { s_cnt = 0; s_ovf = 0; s_fill = 0; }
     if constexpr (SUM)
         for (int t = threadIdx.x; t < AG_HS; t += TILE_BS) { h_key[t] = AG_EMPTY; h_val[t] = 0; }
@@ -156,7 +159,17 @@ __global__ __launch_bounds__(TILE_BS) void k_tile_keys(int32_t n, const int32_t*
             if (u >= m) break;
             const int64_t e = y0 + q0 + u;
             if (e >= rend) {
-                do { ++r; rend = off[r + 1]; } while (e >= rend);
+                ++r;
+                rend = off[r + 1];
+                if (e >= rend) {  // past empty rows: the last row that starts at or before e
+                    int64_t rl = r + 1, rh = last;
+                    while (rl < rh) {
+                        const int64_t mid = (rl + rh + 1) / 2;
+                        if ((int64_t)off[mid] <= e) rl = mid; else rh = mid - 1;
+                    }
+                    r = rl;
+                    rend = off[r + 1];
+                }
                 a = (uint32_t)labels[r];
             }
             const uint32_t b = (uint32_t)jj[u];

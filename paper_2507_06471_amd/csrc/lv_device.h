@@ -129,15 +129,42 @@ __device__ __forceinline__ T block_sum(T v, T* red)
 
 // Merge path over the sequence that interleaves the n row ends (row r ends at
 // position off[r+1] + r) with the nnz CSR entries: the number of row ends
-// among the first d items.
+// among the first d items.  Searched by a whole wavefront (every lane calls it
+// with the same arguments): 64 probes a step narrow the range 64-fold, so that
+// 16 M rows take 4 dependent loads where a binary search takes 24 (and a
+// workgroup does nothing else meanwhile).
 __device__ __forceinline__ int64_t mp_rows(const int32_t* off, int32_t n, int64_t d)
 {
     int64_t lo = 0, hi = n;
     while (lo < hi) {
-        const int64_t mid = (lo + hi) / 2;
-        if ((int64_t)off[mid + 1] + mid < d) lo = mid + 1; else hi = mid;
+        const int64_t step = (hi - lo + WAVE - 1) / WAVE;
+        const int64_t at = lo + (int64_t)lane_id() * step;
+        const bool below = at < hi && (int64_t)off[at + 1] + at < d;  // true for a prefix of the lanes
+        const int64_t k = __popcll(__ballot(below));
+        if (k == 0) return lo;
+        const int64_t last = lo + (k - 1) * step;  // row `last` ends below d
+        hi = last + step < hi ? last + step : hi;
+        lo = last + 1;
     }
     return lo;
+}
+
+// The row of entry e among rows [r, cnt) of ascending starts s_off (s_off[r]
+// <= e < s_off[cnt - 1] or r is the last): the last one that starts at or
+// before e.  The next row is tried first; a run of empty rows is skipped by
+// bisection, not walked: a tile can hold thousands of them, and walking them
+// one LDS read at a time took 72 us in each of R-MAT 16's row copies and packs
+// however few entries the level had (now about 15).
+__device__ __forceinline__ int32_t row_from(const int32_t* s_off, int32_t r, int32_t cnt, int64_t e)
+{
+    if ((int64_t)s_off[r + 1] > e) return r;
+    int32_t lo = r + 1, hi = cnt;  // the first q in (r, cnt) with s_off[q] > e, else cnt
+    if (lo + 1 < cnt && (int64_t)s_off[lo + 1] > e) return lo;
+    while (lo < hi) {
+        const int32_t mid = (lo + hi) >> 1;
+        if ((int64_t)s_off[mid] <= e) lo = mid + 1; else hi = mid;
+    }
+    return lo - 1;
 }
 
 // Visit the CSR entries of merge-path tile `tile` with their row.
@@ -154,7 +181,11 @@ __device__ __forceinline__ void for_tile_entries_at(int64_t tile, const int32_t*
     const int64_t total = (int64_t)n + nnz;
     const int64_t d0 = tile * T;
     const int64_t d1 = d0 + T < total ? d0 + T : total;
-    if (threadIdx.x < 2) s_x[threadIdx.x] = mp_rows(off, n, threadIdx.x ? d1 : d0);
+    static_assert(BS >= 2 * WAVE, "the first two wavefronts search the tile's ends");
+    if (threadIdx.x < 2 * WAVE) {
+        const int64_t x = mp_rows(off, n, threadIdx.x < WAVE ? d0 : d1);
+        if (lane_id() == 0) s_x[threadIdx.x / WAVE] = x;
+    }
     __syncthreads();
     const int64_t x0 = s_x[0], x1 = s_x[1];
     const int64_t y0 = d0 - x0, y1 = d1 - x1;
@@ -169,12 +200,12 @@ __device__ __forceinline__ void for_tile_entries_at(int64_t tile, const int32_t*
         const int64_t mid = (lo + hi) / 2;
         if ((int64_t)s_off[mid] <= my0) lo = mid + 1; else hi = mid;
     }
-    int64_t r = x0 + lo - 1;
+    int32_t r = (int32_t)lo - 1;
     for (int j = 0; j < IT; ++j) {
         const int64_t e = my0 + j;
         if (e >= y1) break;
-        while ((int64_t)s_off[r + 1 - x0] <= e) ++r;
-        f((int32_t)r, e);
+        r = row_from(s_off, r, (int32_t)cnt, e);
+        f((int32_t)(x0 + r), e);
     }
 }
 
@@ -199,7 +230,11 @@ __device__ __forceinline__ void for_tile_entries_co_at(int64_t tile, const int32
     const int64_t total = (int64_t)n + nnz;
     const int64_t d0 = tile * T;
     const int64_t d1 = d0 + T < total ? d0 + T : total;
-    if (threadIdx.x < 2) s_x[threadIdx.x] = mp_rows(off, n, threadIdx.x ? d1 : d0);
+    static_assert(BS >= 2 * WAVE, "the first two wavefronts search the tile's ends");
+    if (threadIdx.x < 2 * WAVE) {
+        const int64_t x = mp_rows(off, n, threadIdx.x < WAVE ? d0 : d1);
+        if (lane_id() == 0) s_x[threadIdx.x / WAVE] = x;
+    }
     __syncthreads();
     const int64_t x0 = s_x[0], x1 = s_x[1];
     const int64_t y0 = d0 - x0, y1 = d1 - x1;
@@ -214,12 +249,12 @@ __device__ __forceinline__ void for_tile_entries_co_at(int64_t tile, const int32
             const int64_t mid = (lo + hi) / 2;
             if ((int64_t)s_off[mid] <= my0) lo = mid + 1; else hi = mid;
         }
-        int64_t r = x0 + lo - 1;
+        int32_t r = (int32_t)lo - 1;
         for (int j = 0; j < IT; ++j) {
             const int64_t e = my0 + j;
             if (e >= y1) break;
-            while ((int64_t)s_off[r + 1 - x0] <= e) ++r;
-            s_row[e - y0] = (int32_t)r;
+            r = row_from(s_off, r, (int32_t)cnt, e);
+            s_row[e - y0] = (int32_t)(x0 + r);
         }
     }
     __syncthreads();

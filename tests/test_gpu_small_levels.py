@@ -110,3 +110,20 @@ def test_both_sides_of_the_size_rule(drop):
     g.name = f"size rule {g.nnz}"
     compare_louvain(g)
     compare_lpa(g)
+
+
+@pytest.mark.parametrize("tuning", [None, {"agg_sort": 1}])
+@pytest.mark.parametrize("gap", [1, 63, 2047, 2048, 4097, 9001])
+def test_runs_of_empty_rows(gap, tuning):
+    # entries between runs of isolated vertices, so that a tile of rows holds none, one or a few
+    at = np.arange(40) * (gap + 1) + gap // 2
+    u = np.concatenate([at[:-1], at[:-3], [at[-1]]])
+    v = np.concatenate([at[1:], at[3:], [at[-1]]])
+    g = graphgen.from_edges(int(at[-1]) + 1 + gap, u, v, 1 + np.arange(len(u)) % 3)
+    g.name = f"gap {gap}"
+    compare_louvain(g, tuning=tuning, keep_graphs=True)
+    compare_louvain(g, tuning=tuning, keep_order=True)
+    compare_lpa(g)
+    with lvp.Graph.from_csr(g) as dg:
+        off, idx, w = dg.csr()
+    assert np.array_equal(off, g.offsets) and np.array_equal(idx, g.indices) and np.array_equal(w, g.weights)
