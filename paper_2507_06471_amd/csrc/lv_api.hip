@@ -16,6 +16,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <map>
 #include <memory>
 #include <mutex>
 #include <new>
@@ -91,19 +92,206 @@ hipError_t dev_alloc(void** p, size_t bytes)
     return hipMalloc(p, bytes ? bytes : 1);
 }
 
-// Grow-only device buffer.
+// Device memory that arenas take from and give back to.  Owned by a server
+// (its jobs' graphs come and go): keeps at most `bound` bytes of slabs for the
+// next job and frees them when it is destroyed.
+struct Slab {
+    char* p = nullptr;
+    size_t size = 0;
+};
+class SlabCache {
+public:
+    explicit SlabCache(size_t bound) : bound_(bound) {}
+    ~SlabCache() { flush(); }
+    SlabCache(const SlabCache&) = delete;
+    SlabCache& operator=(const SlabCache&) = delete;
+    // the smallest kept slab of at least `bytes` (and at most four times that)
+    bool take(size_t bytes, Slab& out)
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        int best = -1;
+        for (int t = 0; t < (int)kept_.size(); ++t)
+            if (kept_[t].size >= bytes && kept_[t].size / 4 <= bytes && (best < 0 || kept_[t].size < kept_[best].size))
+                best = t;
+        if (best < 0) return false;
+        out = kept_[best];
+        held_ -= out.size;
+        kept_.erase(kept_.begin() + best);
+        return true;
+    }
+    void put(const Slab& sl)
+    {
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            if (held_ + sl.size <= bound_) {
+                kept_.push_back(sl);
+                held_ += sl.size;
+                return;
+            }
+        }
+        (void)hipFree(sl.p);
+    }
+    void flush()
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        for (Slab& sl : kept_) (void)hipFree(sl.p);
+        kept_.clear();
+        held_ = 0;
+    }
+
+private:
+    std::mutex mu_;
+    std::vector<Slab> kept_;
+    size_t held_ = 0;
+    const size_t bound_;
+};
+
+// The device memory of one handle: a few large slabs that its buffers are cut
+// from (first fit by size, neighbours joined when freed), given back when the
+// handle goes.  A run on a fresh handle made some 85 allocations, and freeing
+// a block of 4 MiB or more costs 0.2-0.9 ms each (the device is drained and
+// the block unmapped): of the 38 ms that a job of 16 M entries took from host
+// arrays to host labels, 18 were spent there.  Every buffer of an arena is used on the
+// handle's stream (a freed block's next user is ordered after its last) or
+// after the host has waited for that stream.
+class Arena {
+public:
+    explicit Arena(std::shared_ptr<SlabCache> cache = nullptr) : cache_(std::move(cache)) {}
+    ~Arena()
+    {
+        for (auto& r : slabs_) {
+            if (cache_) cache_->put(r.slab);
+            else (void)hipFree(r.slab.p);
+        }
+    }
+    Arena(const Arena&) = delete;
+    Arena& operator=(const Arena&) = delete;
+    // `high`: from the end of the free block (long-lived buffers), so that the
+    // short-lived ones leave one hole, not many.  bytes: a multiple of 256.
+    hipError_t alloc(size_t bytes, bool high, void** out)
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        if (carve(bytes, high, out)) return hipSuccess;
+        // grow by half of what is held, at least 1 MiB and at most 256 MiB more than asked for
+        const size_t extra = std::min<size_t>(std::max<size_t>(held_ / 2, MIN_SLAB), (size_t)256 << 20);
+        hipError_t e = grow(std::max(bytes, extra));
+        if (e == hipErrorOutOfMemory) e = grow(bytes);
+        if (e != hipSuccess) return e;
+        return carve(bytes, high, out) ? hipSuccess : hipErrorOutOfMemory;
+    }
+    void free(void* p, size_t bytes)
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        for (auto& r : slabs_) {
+            if ((char*)p < r.slab.p || (char*)p >= r.slab.p + r.slab.size) continue;
+            size_t at = (size_t)((char*)p - r.slab.p);
+            auto nx = r.free.lower_bound(at);
+            if (nx != r.free.end() && at + bytes == nx->first) {
+                bytes += nx->second;
+                nx = r.free.erase(nx);
+            }
+            if (nx != r.free.begin()) {
+                auto pv = std::prev(nx);
+                if (pv->first + pv->second == at) {
+                    pv->second += bytes;
+                    return;
+                }
+            }
+            r.free.emplace(at, bytes);
+            return;
+        }
+    }
+    // Make sure that about `bytes` are free, in one more slab if they are not
+    // (a hint: a failure is left to the allocations that follow).
+    void reserve(size_t bytes)
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        size_t have = 0;
+        for (auto& r : slabs_)
+            for (auto& f : r.free) have += f.second;
+        if (have < bytes) (void)grow(bytes - have);
+    }
+
+private:
+    static constexpr size_t MIN_SLAB = (size_t)1 << 20;
+    struct Region {
+        Slab slab;
+        std::map<size_t, size_t> free;  // offset -> length, no two adjacent
+    };
+    bool carve(size_t bytes, bool high, void** out)
+    {
+        Region* br = nullptr;
+        std::map<size_t, size_t>::iterator best;
+        for (auto& r : slabs_)
+            for (auto it = r.free.begin(); it != r.free.end(); ++it)
+                if (it->second >= bytes && (!br || it->second < best->second)) {
+                    br = &r;
+                    best = it;
+                }
+        if (!br) return false;
+        const size_t at = best->first, len = best->second;
+        if (high) {
+            *out = br->slab.p + at + (len - bytes);
+            if (len == bytes) br->free.erase(best);
+            else best->second = len - bytes;
+        } else {
+            *out = br->slab.p + at;
+            br->free.erase(best);
+            if (len > bytes) br->free.emplace(at + bytes, len - bytes);
+        }
+        return true;
+    }
+    hipError_t grow(size_t bytes)
+    {
+        bytes = (std::max(bytes, MIN_SLAB) + 0xFFFFF) & ~(size_t)0xFFFFF;
+        Region r;
+        if (!cache_ || !cache_->take(bytes, r.slab)) {
+            void* p = nullptr;
+            hipError_t e = hipMalloc(&p, bytes);
+            if (e == hipErrorOutOfMemory && cache_) {
+                cache_->flush();
+                (void)hipGetLastError();
+                e = hipMalloc(&p, bytes);
+            }
+            if (e != hipSuccess) {
+                (void)hipGetLastError();
+                return e;
+            }
+            r.slab.p = (char*)p;
+            r.slab.size = bytes;
+        }
+        held_ += r.slab.size;
+        r.free.emplace(0, r.slab.size);
+        slabs_.push_back(std::move(r));
+        return hipSuccess;
+    }
+    std::mutex mu_;
+    std::vector<Region> slabs_;
+    size_t held_ = 0;
+    std::shared_ptr<SlabCache> cache_;
+};
+
+// Grow-only device buffer, of an arena or (without one) an allocation of its own.
 struct DevBuf {
     void* p = nullptr;
     size_t cap = 0;
+    std::shared_ptr<Arena> arena;  // where the next allocation comes from
+    bool high = false;
+    std::shared_ptr<Arena> from;   // where p came from
     DevBuf() = default;
+    explicit DevBuf(std::shared_ptr<Arena> a, bool high_ = false) : arena(std::move(a)), high(high_) {}
     DevBuf(const DevBuf&) = delete;
     DevBuf& operator=(const DevBuf&) = delete;
     ~DevBuf() { release(); }
     void release()
     {
-        if (p) (void)hipFree(p);
+        if (p) {
+            if (from) from->free(p, cap);
+            else (void)hipFree(p);
+        }
         p = nullptr;
         cap = 0;
+        from.reset();
     }
     hipError_t ensure(size_t bytes)
     {
@@ -111,7 +299,13 @@ struct DevBuf {
         if (bytes == 0) bytes = 256;
         if (cap >= bytes) return hipSuccess;
         release();
-        hipError_t e = dev_alloc(&p, bytes);
+        hipError_t e;
+        if (arena) {
+            e = fault_now() ? hipErrorOutOfMemory : arena->alloc(bytes, high, &p);
+            if (e == hipSuccess) from = arena;
+        } else {
+            e = dev_alloc(&p, bytes);
+        }
         if (e == hipSuccess) cap = bytes; else p = nullptr;
         return e;
     }
@@ -120,28 +314,42 @@ struct DevBuf {
     {
         std::swap(p, o.p);
         std::swap(cap, o.cap);
+        std::swap(from, o.from);
     }
 };
 
+// Buffers of a handle's workspace.  Per level and call unless said otherwise:
+//   rows: row descriptors of the class-sorted vertices
+//   ce: entry cache: per CSR entry of the handle's input graph, its neighbour's pair
+//   chg: per listed vertex: its pair changed in the last commit (uint8)
+//   rlist, rcnt: per 256-slot tile: its changed rows below the hub class (int4) and their number
+//   mark: active-vertex pruning: last sweep that changed the vertex's neighbourhood
+//   tiles: aggregation: per key tile its count, first entry and output position
+//   p_*: a coarse level stored by degree
+//   a_*, h_*: aggregation by community: entry offsets in member order, segment starts,
+//     distinct counts, long segments' offsets, their sort keys and results
+//   ctl ... segs: per-graph state of a level (G entries) and sweep control
+#define LV_WORKSPACE_BUFFERS(X)                                                                                  \
+    X(comm) X(sigma) X(dec) X(cls) X(vert) X(cls_alt) X(vert_alt) X(minv) X(flag) X(pos) X(labels) X(tmp)        \
+    X(small) X(cs) X(keys) X(keys_alt) X(vals) X(vals_alt) X(head) X(hub_table) X(hub_meta) X(hub_part)          \
+    X(hub_rows) X(hub_cnt) X(hub_bucket) X(hub_bucket_w) X(rows) X(ce) X(chg) X(rlist) X(rcnt) X(mark) X(tiles)  \
+    X(p_off) X(p_idx) X(p_w) X(p_k) X(p_orig) X(p_inv) X(k64) X(a_voff) X(a_seg) X(a_cnt) X(a_hoff) X(a_uoff)    \
+    X(h_keys) X(h_keys_alt) X(h_col) X(h_wt) X(ctl) X(ctr) X(gdone) X(gsweeps) X(gmoves) X(gactive) X(gsum)      \
+    X(gsq) X(gmeta) X(segs)
 struct Workspace {
-    DevBuf comm, sigma, dec, cls, vert, cls_alt, vert_alt, minv, flag, pos, labels, tmp, small, cs;
-    DevBuf keys, keys_alt, vals, vals_alt, head;
+#define LV_X(b) DevBuf b;
+    LV_WORKSPACE_BUFFERS(LV_X)
+#undef LV_X
     DevBuf g_off[2], g_idx[2], g_w[2], g_k[2], g_gid[2];
-    DevBuf hub_table, hub_meta, hub_part, hub_rows, hub_cnt, hub_bucket, hub_bucket_w;
     bool hub_table_clean = false;  // every slot of hub_table is empty
-    DevBuf rows;  // per-level row descriptors of the class-sorted vertices
-    DevBuf ce;    // entry cache: per CSR entry of the handle's input graph, its neighbour's pair
-    DevBuf chg;   // per listed vertex: its pair changed in the last commit (uint8)
-    DevBuf rlist, rcnt;  // per 256-slot tile: its changed rows below the hub class (int4) and their number
-    DevBuf mark;  // active-vertex pruning: last sweep that changed the vertex's neighbourhood
-    DevBuf tiles; // aggregation: per key tile its count, first entry and output position
-    DevBuf p_off, p_idx, p_w, p_k, p_orig, p_inv;  // a coarse level stored by degree
-    DevBuf k64;
-    // aggregation by community: entry offsets in member order, segment starts,
-    // distinct counts, long segments' offsets, their sort keys and results
-    DevBuf a_voff, a_seg, a_cnt, a_hoff, a_uoff, h_keys, h_keys_alt, h_col, h_wt;
-    // per-graph state of a level (G entries) and sweep control
-    DevBuf ctl, ctr, gdone, gsweeps, gmoves, gactive, gsum, gsq, gmeta, segs;
+    explicit Workspace(const std::shared_ptr<Arena>& a)
+    {
+#define LV_X(b) b.arena = a;
+        LV_WORKSPACE_BUFFERS(LV_X)
+#undef LV_X
+        for (int q = 0; q < 2; ++q)
+            for (DevBuf* b : {&g_off[q], &g_idx[q], &g_w[q], &g_k[q], &g_gid[q]}) b->arena = a;
+    }
 };
 
 struct Timer {
@@ -244,49 +452,40 @@ hipError_t pool_take(const std::shared_ptr<BufPool>& pool, size_t bytes, PooledB
 }  // namespace
 
 struct lv_graph {
+    std::shared_ptr<Arena> arena;  // everything the handle itself holds on the device
     int device = 0;
     hipStream_t stream = nullptr;
     bool own_stream = false;
     int32_t n = 0;          // packed vertices
     int64_t nnz = 0;        // packed entries
     int32_t G = 1;          // graphs
-    DevBuf off, idx, w, k;
+    DevBuf off{arena}, idx{arena}, w{arena}, k{arena};
     bool weighted = false;  // false: every A entry is 1 (no weights, no loops)
     std::vector<int32_t> voff;   // [G+1] vertex offset of each graph
     std::vector<int64_t> eoff;   // [G+1] entry offset of each graph
     std::vector<int64_t> M;      // [G] total volume
     std::vector<int64_t> q0;     // [G] Q_int of singletons
     std::vector<int64_t> trace;  // [G] sum of the diagonal entries (loops, doubled)
-    DevBuf d_gid, d_M;           // per vertex graph id, per graph M (G > 1)
+    DevBuf d_gid{arena, true}, d_M{arena, true};           // per vertex graph id, per graph M (G > 1)
     // Storage order: vertices are kept by descending degree within each
     // graph (unless LV_KEEP_ORDER); orig[p] = vertex id at position p,
     // inv[id] = its position.  Every segment of a packed handle keeps its
     // range, so graph ids by position and by id coincide.
     bool reordered = false;
-    DevBuf orig, inv;
+    DevBuf orig{arena, true}, inv{arena, true};
     // Reverse-entry map of the stored input graph: rev[e] = position of the
     // entry (j, i) for the entry e = (i, j) (a loop entry: itself).  Built at
     // creation unless LV_NO_ENTRY_CACHE; used to keep the entry cache current.
-    DevBuf rev;
+    DevBuf rev{arena, true};
     bool has_rev = false;
-    Workspace ws;
+    bool run_reserved = false;
+    Workspace ws{arena};
     int32_t* pinned = nullptr;   // host staging area
     size_t pinned_bytes = 0;
     bool has_tuned = false;      // LV_AUTOTUNE: the setting chosen on first use
     lv_tuning tuned{};
-    // Set-up frees nothing while set (a free waits for the whole device, and
-    // the server sets graphs up while another stream runs): buffers that set-up
-    // would free are parked here until the handle is destroyed.
-    bool keep_scratch = false;
-    std::vector<std::unique_ptr<DevBuf>> parked;
     std::shared_ptr<BufPool> pool = std::make_shared<BufPool>();  // result buffers
-    void release_or_park(DevBuf& b)
-    {
-        if (!b.p) return;
-        if (!keep_scratch) { b.release(); return; }
-        parked.push_back(std::make_unique<DevBuf>());
-        parked.back()->swap(b);
-    }
+    explicit lv_graph(std::shared_ptr<SlabCache> cache = nullptr) : arena(std::make_shared<Arena>(std::move(cache))) {}
     ~lv_graph()
     {
         if (pinned) (void)hipHostFree(pinned);
@@ -1310,6 +1509,7 @@ lv_status aggregate_by_community(lv_graph* g, const LevelGraph& G, int32_t n2, i
         LV_TRY(read_back(g, {{&eh, hoff + nh, sizeof eh}}));
         HIP_TRY(ws.h_keys.ensure(sizeof(uint64_t) * (size_t)std::max(eh, 1)));
         HIP_TRY(ws.h_keys_alt.ensure(sizeof(uint64_t) * (size_t)std::max(eh, 1)));
+        for (DevBuf* b : {&ws.vals, &ws.vals_alt, &ws.head}) HIP_TRY(b->ensure(sizeof(int32_t) * (size_t)std::max(eh, 1)));
         HIP_TRY(ws.tmp.ensure(std::max(radix_tmp_bytes(eh), scan_tmp_bytes(eh, 8))));
         HIP_TRY(launch_long_keys(nh, hv, hoff, eh, seg, col, wt, colbits, ws.h_keys.as<uint64_t>(),
                                  ws.vals.as<int32_t>(), s));
@@ -1365,9 +1565,6 @@ lv_status aggregate(lv_graph* g, const LevelGraph& G, int32_t n2, int32_t isolat
     const int bits = 2 * colbits;
     HIP_TRY(ws.keys.ensure(sizeof(uint64_t) * E1));
     HIP_TRY(ws.keys_alt.ensure(sizeof(uint64_t) * E1));
-    HIP_TRY(ws.vals.ensure(sizeof(int32_t) * E1));
-    HIP_TRY(ws.vals_alt.ensure(sizeof(int32_t) * E1));
-    HIP_TRY(ws.head.ensure(sizeof(int32_t) * E1));
     HIP_TRY(ws.tmp.ensure(std::max(radix_tmp_bytes(E), scan_tmp_bytes(std::max<int64_t>(E, n2 + 1), 8))));
     HIP_TRY(ws.g_off[slot].ensure(sizeof(int32_t) * ((size_t)n2 + 1)));
     HIP_TRY(ws.g_k[slot].ensure(sizeof(int32_t) * (size_t)std::max(n2, 1)));
@@ -1406,6 +1603,8 @@ lv_status aggregate(lv_graph* g, const LevelGraph& G, int32_t n2, int32_t isolat
         out.sorted = false;
         return LV_OK;
     }
+    HIP_TRY(ws.vals.ensure(sizeof(int32_t) * E1));
+    HIP_TRY(ws.vals_alt.ensure(sizeof(int32_t) * E1));
     int64_t Ek = 0;
     LV_TRY(tile_keys(g, agg, G.n, G.off, G.idx, G.w, E, ws.labels.as<int32_t>(), colbits, G.gid, d_sin, &Ek));
     bool in_alt = false;
@@ -1416,6 +1615,7 @@ lv_status aggregate(lv_graph* g, const LevelGraph& G, int32_t n2, int32_t isolat
     uint64_t* keys2 = in_alt ? ws.keys.as<uint64_t>() : ws.keys_alt.as<uint64_t>();  // the free sort buffer
     int32_t* d_e2 = (int32_t*)(ws.small.as<char>() + 2304);
     HIP_TRY(hipMemsetAsync(d_e2, 0, sizeof(int32_t), s));
+    HIP_TRY(ws.head.ensure(sizeof(int32_t) * (size_t)std::max<int64_t>(Ek, 1)));
     HIP_TRY(launch_segment_heads(keys, Ek, ws.head.as<int32_t>(), s));
     if (Ek > 0)
         HIP_TRY(scan_exclusive_i32(ws.head.as<int32_t>(), ws.head.as<int32_t>(), Ek, d_e2, ws.tmp.p, ws.tmp.cap, s));
@@ -1730,12 +1930,19 @@ lv_status louvain_impl(lv_graph* g, const Params& p, bool keep_graphs, lv_result
         HIP_TRY(launch_local_labels(g->n, r->final_labels.i32(), G0 > 1 ? g->d_gid.as<int32_t>() : nullptr,
                                     ws.gmeta.as<int32_t>(), r->final_labels.i32(), s));
     }
+    // one slab for the handle's runs: per entry the entry cache, the aggregation's two
+    // staging arrays and the first coarse graph, per vertex the sweep and
+    // renumbering arrays
+    if (!g->run_reserved) {
+        g->arena->reserve((size_t)g->nnz * 32 + 96 * (size_t)g->n + (64 << 10));
+        g->run_reserved = true;  // the buffers of the first run serve the later ones
+    }
     LevelGraph G = level0(g);
     std::vector<int64_t> eoff = g->eoff;
     std::vector<int32_t> orig(G0);
     for (int32_t q = 0; q < G0; ++q) orig[q] = q;
     std::vector<int64_t> qstart = g->q0;
-    DevBuf Mbuf;
+    DevBuf Mbuf(g->arena);
     int slot = 0;
     Timer tm;
     tm.on = true;  // phase times (renumber, aggregate) are always measured
@@ -1989,7 +2196,7 @@ const char* lv_last_error(void) { return g_last_error.c_str(); }
 static lv_status reorder_by_degree(lv_graph* g, const int32_t* rank)
 {
     if (g->n < 2 || g->nnz == 0) return LV_OK;
-    DevBuf off2, idx2, w2, k2;
+    DevBuf off2(g->arena, true), idx2(g->arena, true), w2(g->arena, true), k2(g->arena, true);
     LV_TRY(degree_order(g, g->n, g->nnz, g->off.as<int32_t>(), g->idx.as<int32_t>(),
                         g->weighted ? g->w.as<int32_t>() : nullptr, g->k.as<int32_t>(),
                         g->G > 1 ? g->d_gid.as<int32_t>() : nullptr, g->G, g->orig, g->inv, off2, idx2, w2, k2, rank,
@@ -2000,7 +2207,7 @@ static lv_status reorder_by_degree(lv_graph* g, const int32_t* rank)
     g->k.swap(k2);
     g->reordered = true;
     Workspace& ws = g->ws;
-    for (DevBuf* b : {&off2, &idx2, &w2, &k2, &ws.keys, &ws.keys_alt, &ws.vals, &ws.vals_alt}) g->release_or_park(*b);
+    for (DevBuf* b : {&off2, &idx2, &w2, &k2, &ws.keys, &ws.keys_alt, &ws.vals, &ws.vals_alt}) b->release();
     return LV_OK;
 }
 
@@ -2027,13 +2234,17 @@ static lv_status graph_setup(lv_graph* g, int32_t n, const int32_t* offsets, con
     g->nnz = nnz;
     g->G = G;
     g->voff = voff;
+    // one slab for the set-up: the given and the stored arrays and the reverse
+    // ranks and map per entry, the sort and storage order per vertex
+    g->arena->reserve((size_t)nnz * ((weights ? 16 : 8) + ((flags & LV_NO_ENTRY_CACHE) ? 0 : 8)) + 64 * (size_t)n +
+                      (64 << 10));
     HIP_TRY(g->idx.ensure(sizeof(int32_t) * (size_t)std::max<int64_t>(nnz, 1)));
     if (nnz > 0) HIP_TRY(hipMemcpyAsync(g->idx.p, indices, sizeof(int32_t) * (size_t)nnz, hk, s));
     Workspace& ws = g->ws;
     HIP_TRY(ws.small.ensure(4096));
     int32_t* d_err = ws.small.as<int32_t>();
     HIP_TRY(hipMemsetAsync(d_err, 0, 16, s));
-    HIP_TRY(g->w.ensure(sizeof(int32_t) * (size_t)std::max<int64_t>(nnz, 1)));
+    if (weights) HIP_TRY(g->w.ensure(sizeof(int32_t) * (size_t)std::max<int64_t>(nnz, 1)));
     if (weights && nnz > 0) HIP_TRY(hipMemcpyAsync(g->w.p, weights, sizeof(int32_t) * (size_t)nnz, hk, s));
     HIP_TRY(launch_check_offsets(n, g->off.as<int32_t>(), nnz, d_err, s));
     int32_t err = 0;
@@ -2069,6 +2280,7 @@ static lv_status graph_setup(lv_graph* g, int32_t n, const int32_t* offsets, con
     g->weighted = weights != nullptr || any != 0;
     HIP_TRY(g->k.ensure(sizeof(int32_t) * (size_t)std::max(n, 1)));
     if (g->weighted) {
+        HIP_TRY(g->w.ensure(sizeof(int32_t) * (size_t)std::max<int64_t>(nnz, 1)));
         int64_t* d_tot = (int64_t*)(ws.small.as<char>() + 64);
         HIP_TRY(hipMemsetAsync(d_tot, 0, sizeof(int64_t), s));
         HIP_TRY(launch_adjacency_weights(n, w_in, diag, nnz, g->w.as<int32_t>(), d_err, s));
@@ -2076,9 +2288,9 @@ static lv_status graph_setup(lv_graph* g, int32_t n, const int32_t* offsets, con
         HIP_TRY(launch_row_sums(n, g->off.as<int32_t>(), g->w.as<int32_t>(), nnz, g->k.as<int32_t>(),
                                 ws.k64.as<int64_t>(), d_tot, s));
         HIP_TRY(hipStreamSynchronize(s));
-        g->release_or_park(ws.k64);
+        ws.k64.release();
     } else {
-        g->release_or_park(g->w);
+        g->w.release();
         HIP_TRY(launch_degree_unit(n, g->off.as<int32_t>(), g->k.as<int32_t>(), s));
     }
     // per-graph M, trace and sum of squared degrees
@@ -2112,7 +2324,7 @@ static lv_status graph_setup(lv_graph* g, int32_t n, const int32_t* offsets, con
         HIP_TRY(hipStreamSynchronize(s));
     }
     // reverse-entry ranks while the rows are still sorted by column
-    DevBuf rank;
+    DevBuf rank(g->arena);
     bool rank_ok = false;
     if (!(flags & LV_NO_ENTRY_CACHE) && nnz > 0) {
         HIP_TRY(rank.ensure(sizeof(int32_t) * (size_t)nnz));
@@ -2134,9 +2346,9 @@ static lv_status graph_setup(lv_graph* g, int32_t n, const int32_t* offsets, con
     return LV_OK;
 }
 
-static lv_status new_graph(void* stream, lv_graph** out)
+static lv_status new_graph(void* stream, lv_graph** out, std::shared_ptr<SlabCache> cache = nullptr)
 {
-    lv_graph* g = new (std::nothrow) lv_graph();
+    lv_graph* g = new (std::nothrow) lv_graph(std::move(cache));
     if (!g) return LV_E_NOMEM;
     hipError_t e = hipGetDevice(&g->device);
     if (e == hipSuccess) {
@@ -2220,7 +2432,7 @@ static lv_status create_from_edges(lv_graph* g, int32_t n, int64_t m, const int3
     Workspace& ws = g->ws;
     LV_TRY(ensure_pinned(g, 4096));
     // the edge list in device memory
-    DevBuf d_src, d_dst, d_w;
+    DevBuf d_src(g->arena), d_dst(g->arena), d_w(g->arena);
     const int32_t* us = src;
     const int32_t* vs = dst;
     const int32_t* ws_in = weights;
@@ -2240,6 +2452,9 @@ static lv_status create_from_edges(lv_graph* g, int32_t n, int64_t m, const int3
     }
     const int cb = bits_for((int64_t)n + 1);
     const int64_t E = 2 * m;
+    // one slab: the keys and weights with their alternates, head flags, and
+    // the merged CSR; the set-up that follows takes its memory from it
+    g->arena->reserve((size_t)E * 36 + 64 * (size_t)n + (64 << 10));
     LV_TRY(sort_workspace(g, E));
     int64_t* d_stats = (int64_t*)(ws.small.as<char>() + 3840);
     int32_t* d_err = ws.small.as<int32_t>();
@@ -2261,7 +2476,7 @@ static lv_status create_from_edges(lv_graph* g, int32_t n, int64_t m, const int3
         set_error_msg("total volume M >= 2^31");
         return LV_E_OVERFLOW;
     }
-    DevBuf off, idx, w;
+    DevBuf off(g->arena), idx(g->arena), w(g->arena);
     int64_t nnz = 0;
     LV_TRY(csr_from_keys(g, E, stats[0], cb, n, off, idx, w, nnz, nullptr));
     d_w.release();
@@ -2312,7 +2527,7 @@ lv_status lv_graph_csr(lv_graph* g, int32_t* offsets, int32_t* indices, int32_t*
     const int cb = bits_for((int64_t)n + 1);
     LV_TRY(sort_workspace(g, g->nnz));
     // keys (id of the row, id of the column): the stored positions mapped back to ids
-    DevBuf ids;
+    DevBuf ids(g->arena);
     const int32_t* labels = g->reordered ? g->orig.as<int32_t>() : nullptr;
     if (!labels) {
         HIP_TRY(ids.ensure(sizeof(int32_t) * (size_t)std::max(n, 1)));
@@ -2324,7 +2539,7 @@ lv_status lv_graph_csr(lv_graph* g, int32_t* offsets, int32_t* indices, int32_t*
     int64_t Ek = 0;
     LV_TRY(tile_keys(g, false, n, g->off.as<int32_t>(), g->idx.as<int32_t>(), g->weighted ? g->w.as<int32_t>() : nullptr,
                      g->nnz, labels, cb, nullptr, d_scratch, &Ek));
-    DevBuf off, idx, w;
+    DevBuf off(g->arena), idx(g->arena), w(g->arena);
     int64_t nnz = 0;
     uint64_t* keys2 = nullptr;
     LV_TRY(csr_from_keys(g, Ek, Ek, cb, n, off, idx, w, nnz, &keys2));
@@ -2644,7 +2859,6 @@ static lv_status modularity_impl(lv_graph* g, const int32_t* labels_dev, int64_t
     int64_t q2[2];
     HIP_TRY(hipMemcpyAsync(q2, d_q, sizeof q2, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    ws.k64.release();
     *q_int = g->M[0] * q2[0] - q2[1];
     return LV_OK;
 }
@@ -2653,7 +2867,7 @@ lv_status lv_probe_gather(lv_graph* g, int32_t reps, double* entries_per_s)
 {
     if (!g || reps < 1 || !entries_per_s) { set_error_msg("lv_probe_gather: null graph/out or reps < 1"); return LV_E_ARG; }
     hipStream_t s = g->stream;
-    DevBuf tab, sink;
+    DevBuf tab, sink;  // not of the arena: the handle keeps nothing of a probe
     HIP_TRY(tab.ensure(sizeof(int2) * (size_t)std::max(g->n, 1)));
     HIP_TRY(sink.ensure(sizeof(unsigned long long)));
     HIP_TRY(hipMemsetAsync(tab.p, 0x5a, sizeof(int2) * (size_t)std::max(g->n, 1), s));
@@ -2767,7 +2981,7 @@ lv_status lv_lpa(lv_graph* g, const lv_params* params, int32_t* labels, lv_memki
     Params p;
     LV_TRY(read_params(params, p));
     LV_TRY(resolve_tuning(g, params, p));
-    DevBuf out;
+    DevBuf out(g->arena);
     HIP_TRY(out.ensure(sizeof(int32_t) * (size_t)std::max(g->n, 1)));
     SweepOut so;
     std::vector<int32_t> voff2;
