@@ -78,6 +78,29 @@ __device__ __forceinline__ void wave_grouped_add(A* arr, int64_t key, T val, boo
     }
 }
 
+// minv[c] = min(minv[c], id) for every valid lane.  The lanes of a wavefront
+// that share the first lane's community take one atomic together (a label held
+// by most vertices, as after label propagation, would otherwise see one atomic
+// per member); the others read the current minimum from L2 first and skip the
+// atomic when it is smaller.  Reached by all lanes of the wavefront.
+__device__ __forceinline__ void min_if_smaller(int32_t* at, int32_t v)
+{
+    if (__hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > v) atomicMin(at, v);
+}
+__device__ __forceinline__ void min_by_community(int32_t* minv, int32_t c, int32_t id, bool ok)
+{
+    const uint64_t live = __ballot(ok);
+    if (live == 0) return;
+    const int leader = __ffsll((unsigned long long)live) - 1;
+    const int32_t lc = __shfl(c, leader);
+    const bool with = ok && c == lc;
+    int32_t m = with ? id : INT32_MAX;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) m = min(m, __shfl_xor(m, d));
+    if ((int)lane_id() == leader) min_if_smaller(&minv[lc], m);
+    if (ok && !with) min_if_smaller(&minv[c], id);
+}
+
 // Reduce (score, community, own-weight) over aligned groups of G lanes (G <= 64).
 template <int G>
 __device__ __forceinline__ void group_reduce(int64_t& s, int32_t& c, int32_t& wo)
@@ -194,7 +217,7 @@ __device__ __forceinline__ void for_tile_entries_at(int64_t tile, const int32_t*
     for (int64_t t = threadIdx.x; t < cnt; t += BS) s_off[t] = off[x0 + t];
     __syncthreads();
     const int64_t my0 = y0 + (int64_t)threadIdx.x * IT;
-    if (my0 >= y1) return;
+    if (my0 >= y1) return;  // (only this function: the caller may synchronise afterwards)
     int64_t lo = 0, hi = cnt;
     while (lo < hi) {
         const int64_t mid = (lo + hi) / 2;

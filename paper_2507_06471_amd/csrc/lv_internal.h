@@ -430,6 +430,57 @@ hipError_t launch_modularity_parts(int32_t n, const int32_t* off, const int32_t*
 
 hipError_t launch_check_labels(const int32_t* labels, int32_t n, int32_t* err, hipStream_t s);
 
+// ---- small levels (lv_small.hip)
+constexpr int SMALL_SCAN_TILE = 8192;              // elements per workgroup of a single-pass scan
+constexpr unsigned long long HASH_EMPTY = ~0ull;   // labels are below 2^31
+// Device-side sizes and counters of a small level, zero at its start.
+struct SmallState {
+    int32_t cls_cnt[16];  // rows per class
+    int32_t cls_cur[16];  // next slot of each class
+    int32_t active0;      // first slot of a row with entries
+    int32_t n2, e2;       // communities, coarse entries
+    uint32_t init_ticket, rank_ticket, row_ticket;
+};
+// In pinned host memory: the class bounds once `ready`, the report once `reported`.
+struct SmallMail {
+    int32_t ready, reported;
+    int32_t start[NUM_CLS + 1];
+};
+struct SmallLevel {
+    int32_t n, G;
+    int64_t nnz;
+    const int32_t *off, *idx, *w, *k, *gid, *orig;
+    int32_t bounds[NUM_CLS];
+    int32_t *comm, *sigma;
+    int2* cs;
+    int32_t* vert;        // listed by class; rows: descriptors of the listed rows with entries
+    int4* rows;
+    int32_t *minv, *flag, *pos, *labels;
+    int32_t* labels_id;   // labels by vertex id (null: not wanted; only with orig)
+    SmallState* st;
+    unsigned long long *scan_rank, *scan_rows;  // look-back states, zero at the level's start
+    int64_t* st_sums;     // [2G] Sigma_in, then the sum of squared volumes
+    SmallMail* mail;
+};
+struct SmallCoarse {
+    int32_t *k2, *gid2;   // k2 null: labels only
+    int32_t* cnt;         // [n] entries of each coarse row, then its next write position
+    unsigned long long* keys;  // hash table of mask + 1 slots, empty between levels
+    int32_t* vals;
+    uint32_t mask;
+    int32_t *off2, *idx2, *w2;  // off2 null: not aggregated here
+};
+struct SmallReport {      // pinned host memory
+    int32_t *voff2, *eoff2;  // [G + 1]
+    int64_t* sums;           // [2G]
+};
+hipError_t launch_level_start(const SmallLevel& a, const SweepEnd& end, const int32_t* gactive, hipStream_t s);
+hipError_t launch_small_renumber(const SmallLevel& a, int32_t active, const SmallCoarse& c, hipStream_t s);
+hipError_t launch_small_aggregate(const SmallLevel& a, const SmallCoarse& c, hipStream_t s);
+hipError_t launch_hash_clear(unsigned long long* keys, int32_t* vals, int64_t slots, hipStream_t s);
+hipError_t launch_small_report(const SmallLevel& a, const SmallCoarse& c, const int32_t* voff, const SmallReport& r,
+                               hipStream_t s);
+
 // ---- aggregation by community (lv_agg.hip)
 // One degree class of coarse vertices: verts[0..m) are coarse vertices whose
 // segments [seg[P], seg[P+1]) of (col, wt) (wt null: unit) are summed; the

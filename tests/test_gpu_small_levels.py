@@ -127,3 +127,47 @@ def test_runs_of_empty_rows(gap, tuning):
     with lvp.Graph.from_csr(g) as dg:
         off, idx, w = dg.csr()
     assert np.array_equal(off, g.offsets) and np.array_equal(idx, g.indices) and np.array_equal(w, g.weights)
+
+
+@pytest.mark.parametrize("n", [1, 2, 1023, 8191, 8192, 8193, 16385, 64 * 8192 + 1, 130 * 8192 + 77])
+def test_scan_tiles(n):
+    # vertex counts around the tiles of the renumbering scan, up to several look-back windows;
+    # a few communities spread over the whole range of ids and both ends
+    rng = np.random.default_rng(n)
+    at = np.unique(np.concatenate([[0, n - 1], rng.integers(0, n, 300)]))
+    u = at[rng.integers(0, len(at), 900)]
+    v = at[rng.integers(0, len(at), 900)]
+    g = graphgen.from_edges(n, u, v, rng.integers(1, 5, 900))
+    g.name = f"scan n={n}"
+    compare_louvain(g, keep_graphs=True)
+    compare_louvain(g, keep_order=True)
+    compare_lpa(g)
+
+
+def test_packed_graphs_with_empty_ones():
+    empty = graphgen.from_edges(0, [], [])
+    lone = graphgen.from_edges(3, [], [])
+    gs = [empty, lone, graphgen.sbm(500, 50, 0.2, 0.002, seed=4), empty, graphgen.from_edges(2, [0, 0], [1, 0]), lone,
+          empty]
+    with lvp.Graph.batch(gs) as bg:
+        got = lvp.louvain(bg)
+    for i, g in enumerate(gs):
+        want = oracle.louvain(g)
+        assert np.array_equal(got[i].final_labels, want.final_labels), i
+        assert got[i].q_int == want.q_int
+
+
+@pytest.mark.parametrize("drop", [1, 0, -1])
+def test_both_sides_of_the_hashing_rule(drop):
+    # 2^20 - 2, 2^20 (the last to be hashed) and 2^20 + 2 entries
+    n = 1 << 15
+    u = np.tile(np.arange(n), 16)
+    v = (u + np.repeat(np.arange(1, 17), n)) % n
+    keep = len(u) - max(drop, 0)
+    u, v = u[:keep], v[:keep]
+    if drop < 0:
+        u, v = np.append(u, 0), np.append(v, n // 2)
+    g = graphgen.from_edges(n, u, v, 1 + (u * 48271 + v * 7) % 6)
+    assert g.nnz == (1 << 20) - 2 * drop
+    g.name = f"hash rule {g.nnz}"
+    compare_louvain(g, keep_graphs=True)
