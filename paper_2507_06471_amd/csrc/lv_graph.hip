@@ -149,8 +149,10 @@ template <bool SQUARE>
 __global__ __launch_bounds__(256) void k_sum_sq(int64_t n, const int32_t* v, const int32_t* gid,
                                                 unsigned long long* out)
 {
+    // contiguous shares: a thread's running sum rarely changes graph
     GraphAcc acc;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    const int64_t end = n * (blockIdx.x + 1) / gridDim.x;
+    for (int64_t i = n * blockIdx.x / gridDim.x + threadIdx.x; i < end; i += 256) {
         const int64_t x = (int64_t)v[i];
         acc.add(out, gid ? gid[i] : 0, (unsigned long long)(SQUARE ? x * x : x));
     }

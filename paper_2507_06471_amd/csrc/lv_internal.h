@@ -312,12 +312,13 @@ struct FusedMap {
     int32_t row_end[NUM_CLS];
 };
 hipError_t launch_move_fused(const MoveArgs& a, const FusedMap& fm, SweepCtl* ctl, hipStream_t s);
-// A whole sweep of a small level but for the pair refresh: every class of fm
-// in one launch (k_move_merged), movers committed at once.  fm's items are
-// blocks of merged_rows(cls) rows; CLS_HUB rows have been decided already
-// (a.dec) and are only committed.
+// Every class of fm in one launch (k_move_merged).  commit (small levels):
+// movers are committed at once, a sweep but for the pair refresh; else they
+// are recorded in a.dec.  fm's items are blocks of merged_rows(cls) rows;
+// CLS_HUB rows (commit only) have been decided already (a.dec) and are only
+// committed.
 int32_t merged_rows(int cls);
-hipError_t launch_move_merged(const MoveArgs& a, const FusedMap& fm, hipStream_t s);
+hipError_t launch_move_merged(const MoveArgs& a, const FusedMap& fm, bool commit, hipStream_t s);
 hipError_t launch_hub_clear(int32_t* table, int64_t slots, hipStream_t s);
 hipError_t launch_chunk_list(const int32_t* first, int32_t nhubs, int32_t total, const int32_t* base,
                              const int32_t* len, int32_t chunk, int32_t* o_hub, int32_t* o_beg, int32_t* o_end,

@@ -865,7 +865,13 @@ __global__ __launch_bounds__(REG_BS) void k_move_reg(MoveArgs a)
 // classes do not use costs nothing where the chip is not full.  Every sweep,
 // the first included, goes through the tables.  Rows of hubs are decided by
 // the partition kernels before this launch and committed here.
+//
+// COMMIT = false (large levels): the same launch for the classes that cannot
+// fill the chip by themselves; decisions are recorded for k_apply.  One after
+// another, each of these classes' launches ends in its longest row's chain of
+// loads and table probes with most of the chip idle.
 constexpr int MERGED_BS = 1024;
+template <bool COMMIT>
 __global__ __launch_bounds__(MERGED_BS) void k_move_merged(MoveArgs a, FusedMap fm)
 {
     __shared__ __align__(16) unsigned long long s_tab[FUSED_SLOTS];
@@ -878,9 +884,10 @@ __global__ __launch_bounds__(MERGED_BS) void k_move_merged(MoveArgs a, FusedMap 
     while (q + 1 < fm.nclass && fm.item_first[q + 1] <= b) ++q;
     const int64_t k = b - fm.item_first[q];
     const int64_t r0 = fm.row_first[q], r1 = fm.row_end[q];
+    const int ecm = COMMIT ? EC_GATHER : entry_mode(a);
 #define LV_MERGED_CASE(C, G, SL)                                                                                   \
     case C:                                                                                                        \
-        claim_rows<C, MERGED_BS, G, SL, true>(a, EC_GATHER, r0 + k * (MERGED_BS / G), r1, s_tab, rs, rc, rw);      \
+        claim_rows<C, MERGED_BS, G, SL, COMMIT>(a, ecm, r0 + k * (MERGED_BS / G), r1, s_tab, rs, rc, rw);          \
         break;
     switch (fm.cls[q]) {
         case CLS_L4:
@@ -888,7 +895,7 @@ __global__ __launch_bounds__(MERGED_BS) void k_move_merged(MoveArgs a, FusedMap 
             const int64_t vi = r0 + k * MERGED_BS + threadIdx.x;
             const bool has = vi < r1;
             const int4 row = has ? a.rows[vi] : make_int4(0, 0, 0, 0);
-            const bool live = has && !vertex_frozen(a, row.x);
+            const bool live = has && !vertex_frozen(a, row.x) && !vertex_skipped(a, row.x);
             int64_t best_s = INT64_MIN;
             int32_t best_c = INT32_MAX, w_own = 0;
             const int2 self = live ? a.cs[row.x] : make_int2(0, 0);
@@ -898,10 +905,11 @@ __global__ __launch_bounds__(MERGED_BS) void k_move_merged(MoveArgs a, FusedMap 
                 mover = best_c >= 0;
             } else if (live) {
                 const int64_t M = vertex_M(a, row.x);
-                reg_best<CLS_CAP[CLS_L4]>(a, EC_GATHER, row.x, row.y, row.z, self.x, row.w, M, best_s, best_c, w_own);
+                reg_best<CLS_CAP[CLS_L4]>(a, ecm, row.x, row.y, row.z, self.x, row.w, M, best_s, best_c, w_own);
                 mover = decide(a, self.x, self.y, row.w, M, best_s, best_c, w_own);
             }
-            commit_movers<MERGED_BS>(a, s_tab, mover, row.x, self.x, best_c, row.w);
+            if constexpr (COMMIT) commit_movers<MERGED_BS>(a, s_tab, mover, row.x, self.x, best_c, row.w);
+            else if (has) a.dec[vi] = mover ? best_c : -1;
             break;
         }
         LV_MERGED_CASE(CLS_L8, 4, L8_SLOTS)
@@ -1891,10 +1899,12 @@ int32_t merged_rows(int cls)
     constexpr int32_t G[NUM_CLS] = {1, 1, 4, 8, 32, 64, 128, 256, 512, 512, 1024, 1};  // lanes per row
     return MERGED_BS / G[cls];
 }
-hipError_t launch_move_merged(const MoveArgs& a, const FusedMap& fm, hipStream_t s)
+hipError_t launch_move_merged(const MoveArgs& a, const FusedMap& fm, bool commit, hipStream_t s)
 {
     if (fm.nclass <= 0 || fm.item_first[fm.nclass] <= 0) return hipSuccess;
-    k_move_merged<<<(unsigned)fm.item_first[fm.nclass], MERGED_BS, 0, s>>>(a, fm);
+    const unsigned grid = (unsigned)fm.item_first[fm.nclass];
+    if (commit) k_move_merged<true><<<grid, MERGED_BS, 0, s>>>(a, fm);
+    else k_move_merged<false><<<grid, MERGED_BS, 0, s>>>(a, fm);
     return hipGetLastError();
 }
 
