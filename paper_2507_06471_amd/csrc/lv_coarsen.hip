@@ -330,16 +330,6 @@ __global__ __launch_bounds__(256) void k_edge_keys(int64_t m, const int32_t* src
     }
 }
 
-// Stored loops are doubled (A_vv = 2w); the caller's convention carries w.
-__global__ void k_halve_diagonal(const uint64_t* keys2, int64_t e2, int cb, int32_t* w2)
-{
-    const uint64_t lo = (1ull << cb) - 1ull;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < e2; e += (int64_t)gridDim.x * blockDim.x) {
-        const uint64_t k = keys2[e];
-        if ((k >> cb) == (k & lo)) w2[e] /= 2;
-    }
-}
-
 __global__ void k_row_offsets(const uint64_t* keys2, int64_t e2, int32_t n2, int colbits, int32_t* off2)
 {
     for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r <= n2; r += (int64_t)gridDim.x * blockDim.x) {
@@ -496,12 +486,6 @@ hipError_t launch_edge_keys(int64_t m, const int32_t* src, const int32_t* dst, c
 {
     if (m <= 0) return hipSuccess;
     k_edge_keys<<<LV_GRID(m)>>>(m, src, dst, w, n, cb, drop_loops ? 1 : 0, keys, vals, (unsigned long long*)stats, err);
-    return hipGetLastError();
-}
-hipError_t launch_halve_diagonal(const uint64_t* keys2, int64_t e2, int cb, int32_t* w2, hipStream_t s)
-{
-    if (e2 <= 0) return hipSuccess;
-    k_halve_diagonal<<<LV_GRID(e2)>>>(keys2, e2, cb, w2);
     return hipGetLastError();
 }
 hipError_t launch_row_offsets(const uint64_t* keys2, int64_t e2, int32_t n2, int colbits, int32_t* off2, hipStream_t s)

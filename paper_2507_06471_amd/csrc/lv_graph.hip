@@ -300,6 +300,28 @@ __global__ __launch_bounds__(TILE_BS) void k_perm_rows(int32_t n, const int32_t*
     });
 }
 
+// A stored CSR in vertex-id order and the caller's convention: row q of the
+// result is the stored row at position inv[q] (null: q), a column the id
+// orig[position] (null: the position).  Storing a graph by degree permutes its
+// rows and keeps each row's entries in order, so the columns come out
+// ascending.  Loops are stored doubled.  w_out null: no weights wanted.
+__global__ __launch_bounds__(TILE_BS) void k_export_rows(int32_t n, const int32_t* off_out, int64_t nnz,
+                                                          const int32_t* inv, const int32_t* orig, const int32_t* off,
+                                                          const int32_t* idx, const int32_t* w, int32_t* idx_out,
+                                                          int32_t* w_out)
+{
+    for_tile_entries_co_at<TILE_BS, TILE_IT>((int64_t)blockIdx.x, off_out, n, nnz, [&](int32_t q, int64_t e) {
+        const int64_t src = (int64_t)off[inv ? inv[q] : q] + (e - off_out[q]);
+        const int32_t p = idx[src];
+        const int32_t id = orig ? orig[p] : p;
+        idx_out[e] = id;
+        if (w_out) {
+            const int32_t x = w ? w[src] : 1;
+            w_out[e] = w && id == q ? x / 2 : x;
+        }
+    });
+}
+
 // Reverse-entry ranks of a CSR with sorted rows.  Each unordered pair {i, j}
 // (i != j) is handled once, by its entry in the longer row (ties: the larger
 // row id), which binary-searches the shorter row for the reverse entry and
@@ -371,6 +393,14 @@ hipError_t launch_perm_rows(int32_t n, const int32_t* off_new, int64_t nnz, cons
     if (nnz <= 0) return hipSuccess;
     k_perm_rows<<<tiles_for(n, nnz), TILE_BS, 0, s>>>(n, off_new, nnz, perm, off, idx, w, inv, idx_new, w_new, rank,
                                                       rev_new);
+    return hipGetLastError();
+}
+hipError_t launch_export_rows(int32_t n, const int32_t* off_out, int64_t nnz, const int32_t* inv, const int32_t* orig,
+                              const int32_t* off, const int32_t* idx, const int32_t* w, int32_t* idx_out,
+                              int32_t* w_out, hipStream_t s)
+{
+    if (nnz <= 0) return hipSuccess;
+    k_export_rows<<<tiles_for(n, nnz), TILE_BS, 0, s>>>(n, off_out, nnz, inv, orig, off, idx, w, idx_out, w_out);
     return hipGetLastError();
 }
 hipError_t launch_reverse_rank(int32_t n, const int32_t* off, const int32_t* idx, int64_t nnz, int32_t* rank,

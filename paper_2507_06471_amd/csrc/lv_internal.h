@@ -396,6 +396,10 @@ hipError_t launch_perm_lengths(const int32_t* perm, int32_t n, const int32_t* of
 hipError_t launch_perm_rows(int32_t n, const int32_t* off_new, int64_t nnz, const int32_t* perm, const int32_t* off,
                             const int32_t* idx, const int32_t* w, const int32_t* inv, int32_t* idx_new, int32_t* w_new,
                             const int32_t* rank, int32_t* rev_new, hipStream_t s);
+// a stored CSR in id order (off_out: its row offsets), loops halved; w_out may be null
+hipError_t launch_export_rows(int32_t n, const int32_t* off_out, int64_t nnz, const int32_t* inv, const int32_t* orig,
+                              const int32_t* off, const int32_t* idx, const int32_t* w, int32_t* idx_out,
+                              int32_t* w_out, hipStream_t s);
 // dst[idx[t]] = src[t]
 hipError_t launch_scatter_i32(const int32_t* src, const int32_t* idx, int32_t m, int32_t* dst, hipStream_t s);
 // keys = (label(i) << colbits) | label(j); sigma_in[g] += weight inside communities (caller zeroes it)
@@ -420,7 +424,6 @@ hipError_t launch_segment_reduce(const uint64_t* keys, const int32_t* vals, cons
 // Edge list -> 2m keys/values (see lv_graph_create_edges); stats = {entries, volume}.
 hipError_t launch_edge_keys(int64_t m, const int32_t* src, const int32_t* dst, const int32_t* w, int32_t n, int cb,
                             bool drop_loops, uint64_t* keys, int32_t* vals, int64_t* stats, int32_t* err, hipStream_t s);
-hipError_t launch_halve_diagonal(const uint64_t* keys2, int64_t e2, int cb, int32_t* w2, hipStream_t s);
 hipError_t launch_row_offsets(const uint64_t* keys2, int64_t e2, int32_t n2, int colbits, int32_t* off2,
                               hipStream_t s);
 hipError_t launch_compose(int32_t n0, int32_t* final_labels, const int32_t* labels, const int32_t* gid0,
