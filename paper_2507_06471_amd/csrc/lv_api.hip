@@ -2441,9 +2441,11 @@ static lv_status reorder_by_degree(lv_graph* g, const int32_t* rank)
 
 // Device setup of a packed CSR (offsets/indices/weights in `kind` memory,
 // graph g at vertices [voff[g], voff[g+1])): validation, loop doubling,
-// degrees, per-graph M and singleton Q_int.
+// degrees, per-graph M and singleton Q_int.  trusted: a CSR the library has
+// built itself (offsets, sorted columns and weights are not checked again).
 static lv_status graph_setup(lv_graph* g, int32_t n, const int32_t* offsets, const int32_t* indices,
-                             const int32_t* weights, lv_memkind kind, uint32_t flags, const std::vector<int32_t>& voff)
+                             const int32_t* weights, lv_memkind kind, uint32_t flags, const std::vector<int32_t>& voff,
+                             bool trusted = false)
 {
     hipStream_t s = g->stream;
     LV_TRY(ensure_pinned(g, 4096));
@@ -2462,10 +2464,12 @@ static lv_status graph_setup(lv_graph* g, int32_t n, const int32_t* offsets, con
     g->nnz = nnz;
     g->G = G;
     g->voff = voff;
-    // one slab for the set-up: the given and the stored arrays and the reverse
-    // ranks and map per entry, the sort and storage order per vertex
-    g->arena->reserve((size_t)nnz * ((weights ? 16 : 8) + ((flags & LV_NO_ENTRY_CACHE) ? 0 : 8)) + 64 * (size_t)n +
-                      (64 << 10));
+    // one slab for the set-up: the given arrays, the order by column and the
+    // reverse ranks per entry (then, in the order's place, the stored arrays
+    // and the reverse map), the storage order per vertex
+    const bool order = (flags & LV_VALIDATE) || !(flags & LV_NO_ENTRY_CACHE);
+    g->arena->reserve((size_t)nnz * ((weights ? 8 : 4) + (order ? 16 : 8) + ((flags & LV_NO_ENTRY_CACHE) ? 0 : 4)) +
+                      64 * (size_t)n + (64 << 10));
     HIP_TRY(g->idx.ensure(sizeof(int32_t) * (size_t)std::max<int64_t>(nnz, 1)));
     if (nnz > 0) HIP_TRY(hipMemcpyAsync(g->idx.p, indices, sizeof(int32_t) * (size_t)nnz, hk, s));
     Workspace& ws = g->ws;
@@ -2480,14 +2484,36 @@ static lv_status graph_setup(lv_graph* g, int32_t n, const int32_t* offsets, con
     HIP_TRY(hipStreamSynchronize(s));
     if (err & 1) { set_error_msg("offsets not non-decreasing or offsets[n] != nnz"); return LV_E_CSR; }
     const int32_t* w_in = weights ? g->w.as<int32_t>() : nullptr;
-    HIP_TRY(launch_check_entries(n, g->off.as<int32_t>(), g->idx.as<int32_t>(), w_in, nnz, d_err, s));
-    if (flags & LV_VALIDATE)
-        HIP_TRY(launch_check_symmetric(n, g->off.as<int32_t>(), g->idx.as<int32_t>(), w_in, nnz, d_err, s));
-    HIP_TRY(hipMemcpyAsync(&err, d_err, sizeof err, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    if (!trusted) {
+        HIP_TRY(launch_check_entries(n, g->off.as<int32_t>(), g->idx.as<int32_t>(), w_in, nnz, d_err, s));
+        HIP_TRY(hipMemcpyAsync(&err, d_err, sizeof err, hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipStreamSynchronize(s));
+    }
     if (err & 2) { set_error_msg("column index out of range or row not strictly increasing"); return LV_E_CSR; }
     if (err & 4) { set_error_msg("weight < 1"); return LV_E_WEIGHT; }
-    if (err & 8) { set_error_msg("entry without a symmetric partner of equal weight"); return LV_E_ASYMMETRIC; }
+    // The reverse of every entry, from the entries' order by column: the
+    // symmetry check and the entry cache's reverse ranks in one.  An asymmetric
+    // graph that need not be validated gets no cache.
+    DevBuf rank(g->arena);
+    bool rank_ok = false;
+    const bool want_rank = !(flags & LV_NO_ENTRY_CACHE) && nnz > 0;
+    if (nnz > 0 && (want_rank || (flags & LV_VALIDATE))) {
+        DevBuf ck(g->arena), cv(g->arena), ck2(g->arena), cv2(g->arena);
+        for (DevBuf* b : {&ck, &cv, &ck2, &cv2}) HIP_TRY(b->ensure(sizeof(int32_t) * (size_t)nnz));
+        if (want_rank) HIP_TRY(rank.ensure(sizeof(int32_t) * (size_t)nnz));
+        HIP_TRY(ws.tmp.ensure(radix_tmp_bytes(nnz)));
+        bool alt = false;
+        HIP_TRY(radix_order_u32((const uint32_t*)g->idx.p, ck.as<uint32_t>(), cv.as<int32_t>(), ck2.as<uint32_t>(),
+                                cv2.as<int32_t>(), nnz, bits_for(std::max(n, 2)), ws.tmp.p, ws.tmp.cap, &alt, s));
+        const bool val = (flags & LV_VALIDATE) != 0;
+        HIP_TRY(launch_reverse_check(n, g->off.as<int32_t>(), g->idx.as<int32_t>(), val ? w_in : nullptr, nnz,
+                                     alt ? cv2.as<int32_t>() : cv.as<int32_t>(),
+                                     want_rank ? rank.as<int32_t>() : nullptr, val ? 8 : 32, 8, d_err, s));
+        HIP_TRY(hipMemcpyAsync(&err, d_err, sizeof err, hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipStreamSynchronize(s));
+        if (err & 8) { set_error_msg("entry without a symmetric partner of equal weight"); return LV_E_ASYMMETRIC; }
+        rank_ok = want_rank && (err & 32) == 0;
+    }
     // graph ids and entry offsets of the packed graphs
     HIP_TRY(ws.gmeta.ensure(sizeof(int32_t) * ((size_t)G + 1)));
     if (G > 1) {
@@ -2550,17 +2576,6 @@ static lv_status graph_setup(lv_graph* g, int32_t n, const int32_t* offsets, con
         HIP_TRY(g->d_M.ensure(sizeof(int64_t) * (size_t)G));
         HIP_TRY(hipMemcpyAsync(g->d_M.p, g->M.data(), sizeof(int64_t) * (size_t)G, hipMemcpyHostToDevice, s));
         HIP_TRY(hipStreamSynchronize(s));
-    }
-    // reverse-entry ranks while the rows are still sorted by column
-    DevBuf rank(g->arena);
-    bool rank_ok = false;
-    if (!(flags & LV_NO_ENTRY_CACHE) && nnz > 0) {
-        HIP_TRY(rank.ensure(sizeof(int32_t) * (size_t)nnz));
-        HIP_TRY(hipMemsetAsync(d_err, 0, sizeof(int32_t), s));
-        HIP_TRY(launch_reverse_rank(n, g->off.as<int32_t>(), g->idx.as<int32_t>(), nnz, rank.as<int32_t>(), d_err, s));
-        HIP_TRY(hipMemcpyAsync(&err, d_err, sizeof err, hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
-        rank_ok = (err & 32) == 0;  // an asymmetric graph (not validated) gets no cache
     }
     g->rev.release();
     if (!(flags & LV_KEEP_ORDER)) LV_TRY(reorder_by_degree(g, rank_ok ? rank.as<int32_t>() : nullptr));
@@ -2710,7 +2725,7 @@ static lv_status create_from_edges(lv_graph* g, int32_t n, int64_t m, const int3
     release_sort_workspace(g);
     const bool unit = (flags & LV_EDGES_SIMPLE) != 0;
     return graph_setup(g, n, off.as<int32_t>(), idx.as<int32_t>(), unit ? nullptr : w.as<int32_t>(), LV_MEM_DEVICE,
-                       flags & (LV_KEEP_ORDER | LV_NO_ENTRY_CACHE), std::vector<int32_t>{0, n});
+                       flags & (LV_KEEP_ORDER | LV_NO_ENTRY_CACHE), std::vector<int32_t>{0, n}, true);
 }
 
 lv_status lv_graph_create_edges(int32_t n, int64_t m, const int32_t* src, const int32_t* dst, const int32_t* weights,

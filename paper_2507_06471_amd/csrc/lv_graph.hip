@@ -34,21 +34,6 @@ __global__ __launch_bounds__(TILE_BS) void k_check_entries(int32_t n, const int3
     });
 }
 
-__global__ __launch_bounds__(TILE_BS) void k_check_symmetric(int32_t n, const int32_t* off, const int32_t* idx,
-                                                              const int32_t* w, int64_t nnz, int32_t* err)
-{
-    for_tile_entries<TILE_BS, TILE_IT>(off, n, nnz, [&](int32_t r, int64_t e) {
-        const int32_t j = idx[e];
-        if (j == r) return;
-        int64_t lo = off[j], hi = off[j + 1];
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) / 2;
-            if (idx[mid] < r) lo = mid + 1; else hi = mid;
-        }
-        if (lo >= off[j + 1] || idx[lo] != r || (w && w[lo] != w[e])) atomicOr(err, 8);
-    });
-}
-
 // diag_pos[i] = entry of the loop (i, i), or -1
 __global__ void k_diag_scan(int32_t n, const int32_t* off, const int32_t* idx, int32_t* diag_pos, int32_t* any)
 {
@@ -322,29 +307,29 @@ __global__ __launch_bounds__(TILE_BS) void k_export_rows(int32_t n, const int32_
     });
 }
 
-// Reverse-entry ranks of a CSR with sorted rows.  Each unordered pair {i, j}
-// (i != j) is handled once, by its entry in the longer row (ties: the larger
-// row id), which binary-searches the shorter row for the reverse entry and
-// writes both ranks; a loop is its own reverse.
-__global__ __launch_bounds__(TILE_BS) void k_reverse_rank(int32_t n, const int32_t* off, const int32_t* idx,
-                                                           int64_t nnz, int32_t* rank, int32_t* err)
+// Symmetry and reverse entries of a CSR with sorted rows, from the stable
+// order of its entries by column: entries are listed row by row, so those of
+// column j come out in the order of their rows, and the t-th of them is the
+// reverse of row j's t-th entry.  rev[e] = the listed entry, checked to lie in
+// row idx[e], to point back, and (w not null) to have the same weight;
+// rank[e] (may be null) = its position in that row.  Structural mismatches set
+// structural_bits in err, weight mismatches weight_bits.  Three sorting passes
+// and two gathers per entry replace a binary search for each of them (twice:
+// once to validate, once for the map).
+__global__ __launch_bounds__(TILE_BS) void k_reverse_check(int32_t n, const int32_t* off, const int32_t* idx,
+                                                            const int32_t* w, int64_t nnz, const int32_t* rev,
+                                                            int32_t* rank, int32_t structural_bits,
+                                                            int32_t weight_bits, int32_t* err)
 {
-    for_tile_entries<TILE_BS, TILE_IT>(off, n, nnz, [&](int32_t r, int64_t e) {
-        const int32_t j = idx[e];
-        const int32_t rb = off[r];
-        if (j == r) { rank[e] = (int32_t)(e - rb); return; }
-        const int32_t jb = off[j], je = off[j + 1];
-        const int32_t dr = off[r + 1] - rb, dj = je - jb;
-        if (!(dj < dr || (dj == dr && j < r))) return;
-        int32_t lo = jb, hi = je;
-        while (lo < hi) {
-            const int32_t mid = lo + (hi - lo) / 2;
-            if (idx[mid] < r) lo = mid + 1; else hi = mid;
-        }
-        if (lo >= je || idx[lo] != r) { atomicOr(err, 32); return; }
-        rank[e] = lo - jb;
-        rank[lo] = (int32_t)(e - rb);
+    int32_t bad = 0;
+    for_tile_entries_co_at<TILE_BS, TILE_IT>((int64_t)blockIdx.x, off, n, nnz, [&](int32_t r, int64_t e) {
+        const int32_t c = idx[e], x = rev[e];
+        const int32_t cb = off[c], ce = off[c + 1];
+        if (x < cb || x >= ce || idx[x] != r) bad |= structural_bits;
+        else if (w && w[x] != w[e]) bad |= weight_bits;
+        if (rank) rank[e] = x - cb;
     });
+    if (bad) atomicOr(err, bad);
 }
 
 __global__ void k_reverse_from_rank(const int32_t* off, const int32_t* idx, int64_t nnz, const int32_t* rank,
@@ -403,11 +388,13 @@ hipError_t launch_export_rows(int32_t n, const int32_t* off_out, int64_t nnz, co
     k_export_rows<<<tiles_for(n, nnz), TILE_BS, 0, s>>>(n, off_out, nnz, inv, orig, off, idx, w, idx_out, w_out);
     return hipGetLastError();
 }
-hipError_t launch_reverse_rank(int32_t n, const int32_t* off, const int32_t* idx, int64_t nnz, int32_t* rank,
-                               int32_t* err, hipStream_t s)
+hipError_t launch_reverse_check(int32_t n, const int32_t* off, const int32_t* idx, const int32_t* w, int64_t nnz,
+                                const int32_t* rev, int32_t* rank, int32_t structural_bits, int32_t weight_bits,
+                                int32_t* err, hipStream_t s)
 {
     if (nnz <= 0) return hipSuccess;
-    k_reverse_rank<<<tiles_for(n, nnz), TILE_BS, 0, s>>>(n, off, idx, nnz, rank, err);
+    k_reverse_check<<<tiles_for(n, nnz), TILE_BS, 0, s>>>(n, off, idx, w, nnz, rev, rank, structural_bits, weight_bits,
+                                                          err);
     return hipGetLastError();
 }
 hipError_t launch_reverse_from_rank(int32_t n, const int32_t* off, const int32_t* idx, int64_t nnz,
@@ -435,13 +422,6 @@ hipError_t launch_check_entries(int32_t n, const int32_t* off, const int32_t* id
 {
     if (nnz <= 0) return hipSuccess;
     k_check_entries<<<tiles_for(n, nnz), TILE_BS, 0, s>>>(n, off, idx, w, nnz, err);
-    return hipGetLastError();
-}
-hipError_t launch_check_symmetric(int32_t n, const int32_t* off, const int32_t* idx, const int32_t* w, int64_t nnz,
-                                  int32_t* err, hipStream_t s)
-{
-    if (nnz <= 0) return hipSuccess;
-    k_check_symmetric<<<tiles_for(n, nnz), TILE_BS, 0, s>>>(n, off, idx, w, nnz, err);
     return hipGetLastError();
 }
 hipError_t launch_diag_scan(int32_t n, const int32_t* off, const int32_t* idx, int32_t* diag_pos, int32_t* any,

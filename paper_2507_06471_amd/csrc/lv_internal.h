@@ -250,14 +250,15 @@ hipError_t radix_sort_u64(uint64_t* keys, int32_t* vals, uint64_t* keys_alt, int
                           int bits, void* tmp, size_t tmp_bytes, bool* result_in_alt, hipStream_t s);
 hipError_t radix_sort_u32(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* vals_alt, int64_t n,
                           int bits, void* tmp, size_t tmp_bytes, bool* result_in_alt, hipStream_t s);
+// the stable order of in[0..n) by bits [0, bits): the indices end up in vals or (in_alt) va
+hipError_t radix_order_u32(const uint32_t* in, uint32_t* keys, int32_t* vals, uint32_t* ka, int32_t* va, int64_t n,
+                           int bits, void* tmp, size_t tb, bool* in_alt, hipStream_t s);
 
 // graph preparation / validation; err bits: 1 offsets, 2 indices, 4 weights,
 // 8 asymmetric, 16 overflow
 hipError_t launch_check_offsets(int32_t n, const int32_t* off, int64_t nnz, int32_t* err, hipStream_t s);
 hipError_t launch_check_entries(int32_t n, const int32_t* off, const int32_t* idx, const int32_t* w,
                                 int64_t nnz, int32_t* err, hipStream_t s);
-hipError_t launch_check_symmetric(int32_t n, const int32_t* off, const int32_t* idx, const int32_t* w,
-                                  int64_t nnz, int32_t* err, hipStream_t s);
 hipError_t launch_diag_scan(int32_t n, const int32_t* off, const int32_t* idx, int32_t* diag_pos,
                             int32_t* any_diag, hipStream_t s);
 hipError_t launch_adjacency_weights(int32_t n, const int32_t* w_in, const int32_t* diag_pos, int64_t nnz,
@@ -357,11 +358,14 @@ hipError_t launch_cache_refresh(int32_t m, const int4* list, const int32_t* cnt,
                                 SweepCtl* ctl, hipStream_t s);
 hipError_t launch_hub_cache_refresh(const MoveArgs& a, const HubArgs& h, const uint8_t* chg_hub, const int32_t* rev,
                                     hipStream_t s);
-// Reverse-entry map of a CSR whose rows are sorted: rank[e] = position of
-// entry e's reverse (j, i) within row j.  err |= 32 if some entry has no
-// reverse (an asymmetric graph).
-hipError_t launch_reverse_rank(int32_t n, const int32_t* off, const int32_t* idx, int64_t nnz, int32_t* rank,
-                               int32_t* err, hipStream_t s);
+// Checks that rev (the stable order of the entries by column) maps every entry
+// of a CSR with sorted rows to its reverse; rank[e] (rank may be null) =
+// position of entry e's reverse (j, i) within row j.  err |= structural_bits
+// if some entry has no reverse (an asymmetric graph), weight_bits if one has
+// another weight (w null: not compared).
+hipError_t launch_reverse_check(int32_t n, const int32_t* off, const int32_t* idx, const int32_t* w, int64_t nnz,
+                                const int32_t* rev, int32_t* rank, int32_t structural_bits, int32_t weight_bits,
+                                int32_t* err, hipStream_t s);
 // rev[e] = off[idx[e]] + rank[e] (rows kept in place)
 hipError_t launch_reverse_from_rank(int32_t n, const int32_t* off, const int32_t* idx, int64_t nnz,
                                     const int32_t* rank, int32_t* rev, hipStream_t s);
@@ -391,7 +395,7 @@ hipError_t launch_degree_keys(int32_t n, const int32_t* off, const int32_t* gid,
 hipError_t launch_max_degree(int32_t n, const int32_t* off, int32_t* out, hipStream_t s);
 hipError_t launch_inverse(const int32_t* perm, int32_t n, int32_t* inv, hipStream_t s);
 hipError_t launch_perm_lengths(const int32_t* perm, int32_t n, const int32_t* off, int32_t* len, hipStream_t s);
-// rank (may be null): the reverse-entry ranks of the old rows (launch_reverse_rank);
+// rank (may be null): the reverse-entry ranks of the old rows (launch_reverse_check);
 // then rev_new receives the reverse-entry map of the permuted CSR
 hipError_t launch_perm_rows(int32_t n, const int32_t* off_new, int64_t nnz, const int32_t* perm, const int32_t* off,
                             const int32_t* idx, const int32_t* w, const int32_t* inv, int32_t* idx_new, int32_t* w_new,

@@ -190,7 +190,7 @@ __global__ __launch_bounds__(256) void k_radix_scatter(const K* keys, const int3
         const int64_t p = base + it * 256 + t;
         const bool valid = p < n;
         const K key = valid ? keys[p] : (K)0;
-        const int32_t v = valid ? vals[p] : 0;
+        const int32_t v = valid ? (vals ? vals[p] : (int32_t)p) : 0;  // null: each element's index
         const uint32_t d = (uint32_t)(key >> shift) & 255u;
         const uint64_t act = __ballot(valid);
         const uint64_t peers = match_digit(d, act);
@@ -227,23 +227,28 @@ __global__ __launch_bounds__(256) void k_radix_scatter(const K* keys, const int3
     }
 }
 
+// first (may be null): the first pass reads its keys from there, each with its
+// index as value, instead of from keys and vals; at least one pass then runs.
 template <typename K>
 hipError_t radix_sort_t(K* keys, int32_t* vals, K* keys_alt, int32_t* vals_alt, int64_t n, int bits, char* tmp,
-                        size_t tmp_bytes, bool* in_alt, hipStream_t s)
+                        size_t tmp_bytes, bool* in_alt, hipStream_t s, const K* first = nullptr)
 {
     *in_alt = false;
-    if (n <= 1 || bits <= 0) return hipSuccess;
+    if (n <= 0 || (!first && (n <= 1 || bits <= 0))) return hipSuccess;
     const int64_t nb = (n + RADIX_TILE - 1) / RADIX_TILE;
     const size_t cbytes = (((size_t)nb * 256 * sizeof(int32_t)) + 255) & ~(size_t)255;
     if (cbytes > tmp_bytes) return hipErrorInvalidValue;
     int32_t* counts = (int32_t*)tmp;
     K* src_k = keys; int32_t* src_v = vals;
     K* dst_k = keys_alt; int32_t* dst_v = vals_alt;
-    for (int shift = 0; shift < bits; shift += 8) {
-        k_radix_hist<K><<<(unsigned)nb, 256, 0, s>>>(src_k, n, shift, counts, (int)nb);
+    for (int shift = 0; shift < bits || (first && shift == 0); shift += 8) {
+        const bool given = first && shift == 0;
+        const K* in_k = given ? first : src_k;
+        const int32_t* in_v = given ? nullptr : src_v;
+        k_radix_hist<K><<<(unsigned)nb, 256, 0, s>>>(in_k, n, shift, counts, (int)nb);
         hipError_t e = scan_exclusive_t<int32_t>(counts, counts, nb * 256, nullptr, tmp + cbytes, tmp_bytes - cbytes, s);
         if (e != hipSuccess) return e;
-        k_radix_scatter<K><<<(unsigned)nb, 256, 0, s>>>(src_k, src_v, dst_k, dst_v, n, shift, counts, (int)nb);
+        k_radix_scatter<K><<<(unsigned)nb, 256, 0, s>>>(in_k, in_v, dst_k, dst_v, n, shift, counts, (int)nb);
         K* tk = src_k; src_k = dst_k; dst_k = tk;
         int32_t* tv = src_v; src_v = dst_v; dst_v = tv;
         *in_alt = !*in_alt;
@@ -317,6 +322,11 @@ hipError_t radix_sort_u64(uint64_t* keys, int32_t* vals, uint64_t* ka, int32_t* 
                           size_t tb, bool* in_alt, hipStream_t s)
 {
     return radix_sort_t<uint64_t>(keys, vals, ka, va, n, bits, (char*)tmp, tb, in_alt, s);
+}
+hipError_t radix_order_u32(const uint32_t* in, uint32_t* keys, int32_t* vals, uint32_t* ka, int32_t* va, int64_t n,
+                           int bits, void* tmp, size_t tb, bool* in_alt, hipStream_t s)
+{
+    return radix_sort_t<uint32_t>(keys, vals, ka, va, n, bits, (char*)tmp, tb, in_alt, s, in);
 }
 hipError_t radix_sort_u32(uint32_t* keys, int32_t* vals, uint32_t* ka, int32_t* va, int64_t n, int bits, void* tmp,
                           size_t tb, bool* in_alt, hipStream_t s)

@@ -1,0 +1,92 @@
+"""Set-up of a graph: the symmetry check and the reverse-entry map, both from
+the stable order of the entries by column.  Asymmetric graphs of every kind
+are refused when validated (and only lose the entry cache when not), symmetric
+ones pass and give the oracle's result from cached sweeps, at vertex counts
+around the sort's digits."""
+import numpy as np
+import pytest
+
+import graphgen
+import oracle
+import paper_2507_06471_amd as lvp
+
+pytestmark = pytest.mark.gpu
+
+ASYMMETRIC = 3
+
+
+def random_graph(n, m, seed, loops=True):
+    rng = np.random.default_rng(seed)
+    u, v = rng.integers(0, n, m), rng.integers(0, n, m)
+    if not loops:
+        u, v = u[u != v], v[u != v]
+    return graphgen.from_edges(n, u, v, rng.integers(1, 9, len(u)))
+
+
+def status(g):
+    try:
+        with lvp.Graph.from_csr(g, validate=True):
+            return 0
+    except lvp.LvError as e:
+        return e.status
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 255, 256, 257, 2047, 65535, 65536, 65537, 70000])
+def test_symmetric_graphs_pass_and_cache(n):
+    g = random_graph(n, 4 * n + 3, n)
+    assert status(g) == 0
+    want = oracle.louvain(g)
+    for keep_order in (False, True):
+        with lvp.Graph.from_csr(g, keep_order=keep_order) as dg:
+            got = lvp.louvain(dg, tuning={"cache_pct": 100})
+            off, idx, w = dg.csr()
+        assert np.array_equal(off, g.offsets) and np.array_equal(idx, g.indices) and np.array_equal(w, g.weights)
+        assert np.array_equal(got.final_labels, want.final_labels) and got.q_int == want.q_int
+        if got.levels[0].info["sweeps"] > 2:
+            assert got.levels[0].info["cached_sweeps"] == got.levels[0].info["sweeps"] - 2
+
+
+@pytest.mark.parametrize("seed", range(6))
+@pytest.mark.parametrize("kind", ["missing", "moved", "weight", "one_way_rows"])
+def test_asymmetric_graphs_are_refused(kind, seed):
+    n = [40, 300, 5000][seed % 3]
+    g = random_graph(n, 5 * n, 100 + seed, loops=seed % 2 == 0)
+    row = np.repeat(np.arange(n), np.diff(g.offsets))
+    off, idx, w = g.offsets.copy(), g.indices.copy(), g.weights.copy()
+    cand = np.flatnonzero(row != idx)
+    e = int(cand[(seed * 7919) % len(cand)])
+    if kind == "weight":
+        w[e] += 1
+    elif kind == "missing":
+        idx, w = np.delete(idx, e), np.delete(w, e)
+        off[row[e] + 1:] -= 1
+    elif kind == "moved":  # (r, c) -> (r, c') with c' not yet in the row: equal counts, no partner
+        r = row[e]
+        have = set(idx[off[r]:off[r + 1]].tolist())
+        c = next(x for x in range(n) if x not in have and x != r)
+        seg = np.arange(off[r], off[r + 1])
+        idx[e] = c
+        o = np.argsort(idx[seg], kind="stable")
+        idx[seg], w[seg] = idx[seg][o], w[seg][o]
+    else:  # two rows trade an entry's target: in- and out-degrees stay what they were
+        e2 = next(int(x) for x in cand[::-1]
+                  if row[x] != row[e] and idx[x] != idx[e] and row[x] != idx[e] and row[e] != idx[x]
+                  and idx[x] not in idx[off[row[e]]:off[row[e] + 1]]
+                  and idx[e] not in idx[off[row[x]]:off[row[x] + 1]])
+        idx[e], idx[e2] = idx[e2], idx[e]
+        for r in (row[e], row[e2]):
+            seg = np.arange(off[r], off[r + 1])
+            o = np.argsort(idx[seg], kind="stable")
+            idx[seg], w[seg] = idx[seg][o], w[seg][o]
+    bad = graphgen.CSR(n, off.astype(np.int32), idx.astype(np.int32), w.astype(np.int32))
+    assert status(bad) == ASYMMETRIC
+    with lvp.Graph.from_csr(bad, validate=False) as dg:  # taken unchecked, without the cache unless only a weight differs
+        got = lvp.louvain(dg, tuning={"cache_pct": 100}, max_sweeps=6)
+    assert (got.levels[0].info["cached_sweeps"] > 0) <= (kind == "weight")
+
+
+def test_validation_with_the_cache_left_out():
+    g = random_graph(3000, 20000, 9)
+    with lvp.Graph.from_csr(g, validate=True, entry_cache=False) as dg:
+        got = lvp.louvain(dg)
+    assert np.array_equal(got.final_labels, oracle.louvain(g).final_labels)
