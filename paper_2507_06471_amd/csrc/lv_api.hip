@@ -2335,14 +2335,31 @@ lv_status lpa_impl(lv_graph* g, const Params& p, int32_t* out_dev, SweepOut& so,
     LevelGraph G = level0(g);
     g->phase.used = 0;
     LV_TRY(run_sweeps(g, G, MODE_LPA, p, nullptr, so));
-    Timer tm;
-    tm.on = true;
-    tm.s = s;
     hipEvent_t t0{}, t1{};
-    if (tm.on) HIP_TRY(tm.mark(&t0));
+    g->phase.s = s;
+    if (g->small_ok && G.G == 1) {
+        // one small graph: everything after the sweeps in one wait, the labels
+        // written in vertex-id order as they are found
+        SmallLevel& sl = g->small;
+        HIP_TRY(launch_sigma_in(G.n, G.off, G.idx, G.w, G.nnz, ws.comm.as<int32_t>(), nullptr, sl.st_sums, s));
+        HIP_TRY(launch_sum_sq(ws.sigma.as<int32_t>(), G.n, nullptr, sl.st_sums + 1, s));
+        if (G.orig) sl.labels_id = out_dev;
+        else sl.labels = out_dev;
+        const SmallCoarse none{};
+        HIP_TRY(g->phase.mark(&t0));
+        HIP_TRY(launch_small_renumber(sl, g->small_active, none, s));
+        HIP_TRY(g->phase.mark(&t1));
+        std::vector<int64_t> sums;
+        LV_TRY(small_report(g, G, none, voff2, nullptr, &sums));
+        q_int.assign(1, G.Mh[0] * sums[0] - sums[1]);
+        *ren_ms = elapsed(t0, t1);
+        settle_times(so);
+        return LV_OK;
+    }
+    HIP_TRY(g->phase.mark(&t0));
     int32_t n2 = 0;
     LV_TRY(renumber(g, G, &n2, voff2));
-    if (tm.on) HIP_TRY(tm.mark(&t1));
+    HIP_TRY(g->phase.mark(&t1));
     // Q_int of each graph's partition: M * Sigma_in - sum of its community volumes squared
     HIP_TRY(ws.gsum.ensure(sizeof(int64_t) * (size_t)G.G));
     HIP_TRY(ws.gsq.ensure(sizeof(int64_t) * (size_t)G.G));
@@ -2376,7 +2393,7 @@ lv_status lpa_impl(lv_graph* g, const Params& p, int32_t* out_dev, SweepOut& so,
     if (cached) sin[0] += g->trace[0];
     q_int.resize(G.G);
     for (int32_t c = 0; c < G.G; ++c) q_int[c] = G.Mh[c] * sin[c] - sq[c];
-    *ren_ms = tm.on ? elapsed(t0, t1) : 0.0;
+    *ren_ms = elapsed(t0, t1);
     settle_times(so);
     return LV_OK;
 }
@@ -3086,28 +3103,29 @@ lv_status lv_result_destroy(lv_result* r)
     return LV_OK;
 }
 
+// Q_int of labels given by vertex id in device memory: four launches and one
+// wait, whatever the labels (a bad one is found on the way).
 static lv_status modularity_impl(lv_graph* g, const int32_t* labels_dev, int64_t* q_int)
 {
     Workspace& ws = g->ws;
     hipStream_t s = g->stream;
     const int32_t n = g->n;
-    HIP_TRY(ws.k64.ensure(sizeof(int64_t) * (size_t)std::max(n, 1)));
-    int64_t* d_q = (int64_t*)(ws.small.as<char>() + 2816);
-    int32_t* d_err = (int32_t*)(ws.small.as<char>() + 3072);
-    HIP_TRY(hipMemsetAsync(ws.k64.p, 0, sizeof(int64_t) * (size_t)std::max(n, 1), s));
-    HIP_TRY(hipMemsetAsync(d_q, 0, 2 * sizeof(int64_t), s));
-    HIP_TRY(hipMemsetAsync(d_err, 0, sizeof(int32_t), s));
-    HIP_TRY(launch_check_labels(labels_dev, n, d_err, s));
-    int32_t err = 0;
-    HIP_TRY(hipMemcpyAsync(&err, d_err, sizeof err, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    if (err) { set_error_msg("labels must lie in [0, n)"); return LV_E_ARG; }
-    HIP_TRY(launch_modularity_parts(n, g->off.as<int32_t>(), g->idx.as<int32_t>(), g->weighted ? g->w.as<int32_t>() : nullptr,
-                                    g->nnz, g->k.as<int32_t>(), labels_dev, ws.k64.as<int64_t>(), d_q, s));
-    int64_t q2[2];
-    HIP_TRY(hipMemcpyAsync(q2, d_q, sizeof q2, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    *q_int = g->M[0] * q2[0] - q2[1];
+    *q_int = 0;
+    if (n == 0) return LV_OK;
+    HIP_TRY(ws.k64.ensure(256 + sizeof(int32_t) * (size_t)n));
+    if (g->reordered) HIP_TRY(ws.pos.ensure(sizeof(int32_t) * ((size_t)n + 1)));
+    LV_TRY(ensure_pinned(g, 4096));
+    void* dp = nullptr;
+    HIP_TRY(hipHostGetDevicePointer(&dp, g->pinned, 0));
+    ModMail* mail = (ModMail*)g->pinned;
+    mail->ready = 0;
+    HIP_TRY(launch_fill_i32(ws.k64.as<int32_t>(), 0, 64 + (int64_t)n, s));
+    HIP_TRY(launch_modularity(n, g->off.as<int32_t>(), g->idx.as<int32_t>(), g->weighted ? g->w.as<int32_t>() : nullptr,
+                              g->nnz, g->k.as<int32_t>(), labels_dev, g->reordered ? g->orig.as<int32_t>() : nullptr,
+                              ws.pos.as<int32_t>(), ws.k64.as<int32_t>() + 64, ws.k64.as<ModSums>(), (ModMail*)dp, s));
+    LV_TRY(await_flag(s, &mail->ready));
+    if (mail->err) { set_error_msg("labels must lie in [0, n)"); return LV_E_ARG; }
+    *q_int = g->M[0] * mail->sums[0] - mail->sums[1];
     return LV_OK;
 }
 
@@ -3161,22 +3179,21 @@ lv_status lv_modularity(lv_graph* g, const int32_t* labels, lv_memkind kind, int
     if (!g || !labels || (kind != LV_MEM_HOST && kind != LV_MEM_DEVICE)) return LV_E_ARG;
     if (g->G != 1) { set_error_msg("lv_modularity takes a single-graph handle"); return LV_E_STATE; }
     Workspace& ws = g->ws;
-    HIP_TRY(ws.small.ensure(4096));
     const int32_t* dl = labels;
-    SyncOnExit sync_labels{g->stream};  // the caller's labels need to live only for the call
     if (kind == LV_MEM_HOST) {
         HIP_TRY(ws.labels.ensure(sizeof(int32_t) * (size_t)std::max(g->n, 1)));
         if (g->n > 0)
             HIP_TRY(hipMemcpyAsync(ws.labels.p, labels, sizeof(int32_t) * (size_t)g->n, hipMemcpyHostToDevice, g->stream));
         dl = ws.labels.as<int32_t>();
     }
-    if (g->reordered && g->n > 0) {  // to storage positions
-        HIP_TRY(ws.pos.ensure(sizeof(int32_t) * ((size_t)g->n + 1)));
-        HIP_TRY(launch_gather_i32(dl, g->orig.as<int32_t>(), g->n, ws.pos.as<int32_t>(), g->stream));
-        dl = ws.pos.as<int32_t>();
-    }
+    // the caller's labels need to live only for the call: everything that
+    // reads them is done once the results are in
     int64_t qi = 0;
-    LV_TRY(modularity_impl(g, dl, &qi));
+    const lv_status st = modularity_impl(g, dl, &qi);
+    if (st != LV_OK) {
+        (void)hipStreamSynchronize(g->stream);
+        return st;
+    }
     const int64_t M = g->M[0];
     if (q_int) *q_int = qi;
     if (m) *m = M;

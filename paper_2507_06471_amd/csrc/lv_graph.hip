@@ -201,32 +201,26 @@ __global__ __launch_bounds__(TILE_BS) void k_sigma_in_cached(int32_t n, const in
     acc.flush_block(out);
 }
 
-// tot[label] += k_i, one atomic per distinct label of a wavefront
-__global__ __launch_bounds__(256) void k_label_volumes(int32_t n, const int32_t* k, const int32_t* labels,
-                                                       unsigned long long* tot)
-{
-    for (int64_t base = (int64_t)blockIdx.x * 256; base < n; base += (int64_t)gridDim.x * 256) {
-        const int64_t i = base + threadIdx.x;
-        const bool valid = i < n;
-        const int32_t lab = valid ? labels[i] : 0;
-        const unsigned long long kv = valid ? (unsigned long long)k[i] : 0ull;
-        wave_grouped_add<unsigned long long, unsigned long long>(tot, lab, kv, valid);
-    }
-}
-
-__global__ __launch_bounds__(256) void k_sum_sq_u64(const unsigned long long* v, int64_t n, unsigned long long* out)
+// The sum of squared volumes, added to out->sums[1]; the last workgroup posts
+// all three results to pinned memory (mail null: not), in the launch that
+// finds them.
+__global__ __launch_bounds__(256) void k_mod_finish(const int32_t* vol, int64_t n, ModSums* out, ModMail* mail)
 {
     __shared__ unsigned long long red[4];
     unsigned long long s = 0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) s += v[i] * v[i];
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+        s += (unsigned long long)((int64_t)vol[i] * vol[i]);
     s = block_sum<256>(s, red);
-    if (threadIdx.x == 0 && s) atomicAdd(out, s);
-}
-
-__global__ void k_check_labels(const int32_t* labels, int32_t n, int32_t* err)
-{
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        if (labels[i] < 0 || labels[i] >= n) atomicOr(err, 1);
+    if (threadIdx.x != 0) return;
+    if (s) atomicAdd((unsigned long long*)&out->sums[1], s);
+    if (!mail) return;
+    __builtin_amdgcn_s_waitcnt(0);  // the sum before the ticket
+    if (atomicAdd(&out->ticket, 1u) + 1u != gridDim.x) return;
+    mail->sums[0] = out->sums[0];  // of the launch before this one
+    mail->sums[1] = (int64_t)atomicAdd((unsigned long long*)&out->sums[1], 0ull);
+    mail->err = out->err;
+    __threadfence_system();
+    __hip_atomic_store(&mail->ready, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ---- storage order by descending degree
@@ -492,22 +486,16 @@ hipError_t launch_sigma_in_cached(int32_t n, const int32_t* off, const int2* ce,
                                                                                      (unsigned long long*)out);
     return hipGetLastError();
 }
-hipError_t launch_modularity_parts(int32_t n, const int32_t* off, const int32_t* idx, const int32_t* w, int64_t nnz,
-                                   const int32_t* k, const int32_t* labels, int64_t* tot, int64_t* out2, hipStream_t s)
+hipError_t launch_modularity(int32_t n, const int32_t* off, const int32_t* idx, const int32_t* w, int64_t nnz,
+                             const int32_t* k, const int32_t* labels, const int32_t* orig, int32_t* pos, int32_t* vol,
+                             ModSums* out, ModMail* mail, hipStream_t s)
 {
-    if (n > 0) k_label_volumes<<<grid_for(n, 256, 65536), 256, 0, s>>>(n, k, labels, (unsigned long long*)tot);
+    hipError_t e = launch_mod_volumes(n, k, labels, orig, pos, vol, &out->err, s);
+    if (e != hipSuccess) return e;
     if (nnz > 0)
-        k_sigma_in<<<std::min(tiles_for(n, nnz), SUM_GRID), TILE_BS, 0, s>>>(n, off, idx, w, nnz, labels, nullptr,
-                                                         (unsigned long long*)out2);
-    if (n > 0)
-        k_sum_sq_u64<<<grid_for(n, 256, VSUM_GRID), 256, 0, s>>>((const unsigned long long*)tot, n,
-                                                            (unsigned long long*)(out2 + 1));
-    return hipGetLastError();
-}
-hipError_t launch_check_labels(const int32_t* labels, int32_t n, int32_t* err, hipStream_t s)
-{
-    if (n <= 0) return hipSuccess;
-    k_check_labels<<<LV_GRID(n)>>>(labels, n, err);
+        k_sigma_in<<<std::min(tiles_for(n, nnz), SUM_GRID), TILE_BS, 0, s>>>(n, off, idx, w, nnz, orig ? pos : labels,
+                                                         nullptr, (unsigned long long*)&out->sums[0]);
+    k_mod_finish<<<grid_for(n, 1024, VSUM_GRID), 256, 0, s>>>(vol, n, out, mail);
     return hipGetLastError();
 }
 

@@ -432,11 +432,25 @@ hipError_t launch_row_offsets(const uint64_t* keys2, int64_t e2, int32_t n2, int
                               hipStream_t s);
 hipError_t launch_compose(int32_t n0, int32_t* final_labels, const int32_t* labels, const int32_t* gid0,
                           const int32_t* slot, const int32_t* vbase, const int32_t* nbase, hipStream_t s);
-hipError_t launch_modularity_parts(int32_t n, const int32_t* off, const int32_t* idx, const int32_t* w,
-                                   int64_t nnz, const int32_t* k, const int32_t* labels, int64_t* tot,
-                                   int64_t* out2, hipStream_t s);
-
-hipError_t launch_check_labels(const int32_t* labels, int32_t n, int32_t* err, hipStream_t s);
+// Modularity of labels given by vertex id: out->sums = {Sigma_in, sum of
+// squared volumes}, out->err != 0 if a label lies outside [0, n).  out and
+// vol[0..n) are zero on entry; with orig (vertex id of each position), pos[0..n)
+// receives the labels by position.  mail (pinned, may be null) receives the
+// results, then `ready`.
+struct ModSums {
+    int64_t sums[2];
+    int32_t err;
+    uint32_t ticket;
+};
+struct ModMail {
+    int64_t sums[2];
+    int32_t err, ready;
+};
+hipError_t launch_mod_volumes(int32_t n, const int32_t* k, const int32_t* labels, const int32_t* orig, int32_t* pos,
+                              int32_t* vol, int32_t* err, hipStream_t s);
+hipError_t launch_modularity(int32_t n, const int32_t* off, const int32_t* idx, const int32_t* w, int64_t nnz,
+                             const int32_t* k, const int32_t* labels, const int32_t* orig, int32_t* pos, int32_t* vol,
+                             ModSums* out, ModMail* mail, hipStream_t s);
 
 // ---- small levels (lv_small.hip)
 constexpr int SMALL_SCAN_TILE = 8192;              // elements per workgroup of a single-pass scan

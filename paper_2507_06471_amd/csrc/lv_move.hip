@@ -1484,6 +1484,38 @@ __global__ __launch_bounds__(256) void k_volumes(const int32_t* verts, int32_t m
         if (t_key[t] != EMPTY_KEY && t_val[t] != 0) atomicAdd(&sigma[t_key[t]], t_val[t]);
 }
 
+// Modularity's pass over the vertices: each one's label, by position where
+// rows are stored out of id order; labels outside [0, n) flagged and left out;
+// vol[label] += k (summed per workgroup as above; volumes are below 2^31, as
+// the library rejects a larger total).
+__global__ __launch_bounds__(256) void k_mod_volumes(int32_t n, const int32_t* k, const int32_t* labels,
+                                                     const int32_t* orig, int32_t* pos, int32_t* vol, int32_t* err)
+{
+    __shared__ int32_t t_key[APPLY_SLOTS];
+    __shared__ int32_t t_val[APPLY_SLOTS];
+    __shared__ int32_t t_fill;
+    if (threadIdx.x == 0) t_fill = 0;
+    for (int t = threadIdx.x; t < APPLY_SLOTS; t += 256) { t_key[t] = EMPTY_KEY; t_val[t] = 0; }
+    __syncthreads();
+    bool bad = false;
+    for (int64_t base = (int64_t)blockIdx.x * 256; base < n; base += (int64_t)gridDim.x * 256) {
+        const int64_t i = base + threadIdx.x;
+        const bool in = i < n;
+        int32_t C = 0, kv = 0;
+        if (in) {
+            C = labels[orig ? orig[i] : i];
+            kv = k[i];
+            if (orig) pos[i] = C;
+            bad = bad || C < 0 || C >= n;
+        }
+        peeled_apply(t_key, t_val, &t_fill, vol, C, kv, in && C >= 0 && C < n);
+    }
+    if (bad) atomicOr(err, 1);
+    __syncthreads();
+    for (int t = threadIdx.x; t < APPLY_SLOTS; t += 256)
+        if (t_key[t] != EMPTY_KEY && t_val[t] != 0) atomicAdd(&vol[t_key[t]], t_val[t]);
+}
+
 // After sweep s (1-based): a running graph stops when s >= 2 and its last two
 // sweeps moved at most theta vertices each, or when s == max_sweeps.  Sets
 // all_done when no graph runs any more, so later sweeps' kernels exit early.
@@ -2019,6 +2051,13 @@ hipError_t launch_apply(const int32_t* verts, const int32_t* dec, int32_t m, con
 {
     if (m <= 0) return hipSuccess;
     k_apply<<<grid_for(m, 256, 2048), 256, 0, s>>>(verts, dec, m, k, gid, comm, sigma, ctl, ctr, gmoves, max_sweeps);
+    return hipGetLastError();
+}
+hipError_t launch_mod_volumes(int32_t n, const int32_t* k, const int32_t* labels, const int32_t* orig, int32_t* pos,
+                              int32_t* vol, int32_t* err, hipStream_t s)
+{
+    if (n <= 0) return hipSuccess;
+    k_mod_volumes<<<grid_for(n, 1024, 2048), 256, 0, s>>>(n, k, labels, orig, pos, vol, err);
     return hipGetLastError();
 }
 hipError_t launch_volumes(const int32_t* verts, int32_t m, const int32_t* k, const int32_t* comm, int32_t* sigma,

@@ -389,12 +389,10 @@ __global__ __launch_bounds__(256) void k_small_report(SmallLevel a, SmallCoarse 
         const int32_t at = voff ? voff[g] : (g == 0 ? 0 : a.n);
         const int32_t v = at < a.n ? a.pos[at] : n2;
         r.voff2[g] = v;
-        if (c.off2) {
-            r.eoff2[g] = n2 > 0 ? c.off2[v] : 0;
-            if (g < a.G) {
-                r.sums[g] = a.st_sums[g];
-                r.sums[a.G + g] = a.st_sums[a.G + g];
-            }
+        if (c.off2) r.eoff2[g] = n2 > 0 ? c.off2[v] : 0;
+        if (g < a.G) {
+            r.sums[g] = a.st_sums[g];
+            r.sums[a.G + g] = a.st_sums[a.G + g];
         }
     }
     __threadfence_system();

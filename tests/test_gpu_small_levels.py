@@ -171,3 +171,29 @@ def test_both_sides_of_the_hashing_rule(drop):
     assert g.nnz == (1 << 20) - 2 * drop
     g.name = f"hash rule {g.nnz}"
     compare_louvain(g, keep_graphs=True)
+
+
+@pytest.mark.parametrize("n", [1, 5, 256, 1023, 4097, 300000])
+@pytest.mark.parametrize("kind", ["one", "own", "few", "random"])
+def test_modularity_of_labels(n, kind):
+    # one community, every vertex its own, a handful, and more than a workgroup's table holds
+    rng = np.random.default_rng(n)
+    m = 3 * n
+    g = graphgen.from_edges(n, rng.integers(0, n, m), rng.integers(0, n, m), rng.integers(1, 9, m))
+    lab = {"one": np.full(n, n - 1), "own": rng.permutation(n), "few": rng.integers(0, min(n, 5), n),
+           "random": rng.integers(0, n, n)}[kind].astype(np.int32)
+    row = np.repeat(np.arange(n), np.diff(g.offsets))
+    a = g.weights.astype(np.int64) * np.where(row == g.indices, 2, 1)
+    k = np.bincount(row, weights=a, minlength=n).astype(np.int64)
+    vol = np.zeros(n, dtype=np.int64)
+    np.add.at(vol, lab, k)
+    M = int(k.sum())
+    want = M * int(a[lab[row] == lab[g.indices]].sum()) - int((vol * vol).sum())
+    bad = lab.copy()
+    bad[n // 2] = n if n % 2 else -1
+    for keep_order in (False, True):
+        with lvp.Graph.from_csr(g, keep_order=keep_order) as dg:
+            assert lvp.modularity(dg, lab)[:2] == (want, M)
+            with pytest.raises(lvp.LvError):
+                lvp.modularity(dg, bad)
+            assert lvp.modularity(dg, lab)[:2] == (want, M)
