@@ -244,7 +244,7 @@ hipError_t scan_exclusive_i64(const int64_t* in, int64_t* out, int64_t n, int64_
                               size_t tmp_bytes, hipStream_t s);
 size_t scan_tmp_bytes(int64_t n, size_t elem);
 
-// stable LSD radix sort of (key, value) pairs on key bits [0, bits)
+// stable LSD radix sort of (key, value) pairs on key bits [0, bits) (vals and vals_alt null: keys alone)
 size_t radix_tmp_bytes(int64_t n);
 hipError_t radix_sort_u64(uint64_t* keys, int32_t* vals, uint64_t* keys_alt, int32_t* vals_alt, int64_t n,
                           int bits, void* tmp, size_t tmp_bytes, bool* result_in_alt, hipStream_t s);
@@ -421,8 +421,11 @@ hipError_t launch_compact_tiles(const uint64_t* keys, const int32_t* vals, const
 // rebuild a packed CSR (off[n_out+1], idx/w[nnz_out], k, gid) from device segment descriptors
 hipError_t launch_repack(const RepackSeg* seg, int32_t nseg, int32_t n_out, int64_t nnz_out, int32_t* off, int32_t* idx,
                          int32_t* w, int32_t* k, int32_t* gid, int32_t* orig, hipStream_t s);
-hipError_t launch_segment_heads(const uint64_t* keys, int64_t n, int32_t* head, hipStream_t s);
-// w2 must be zeroed; writes idx2/w2/keys2 of each run of equal keys
+// runs of equal keys begun in each of the run_tiles(n) tiles of n sorted keys
+int64_t run_tiles(int64_t n);
+hipError_t launch_run_counts(const uint64_t* keys, int64_t n, int32_t* counts, hipStream_t s);
+// idx2/w2/keys2 of each run; pos = the counts' exclusive scan; w2 zeroed, or
+// null: not wanted; vals null: every weight is 1
 hipError_t launch_segment_reduce(const uint64_t* keys, const int32_t* vals, const int32_t* pos, int64_t n,
                                  int colbits, int32_t* idx2, int32_t* w2, uint64_t* keys2, hipStream_t s);
 // Edge list -> 2m keys/values (see lv_graph_create_edges); stats = {entries, volume}.

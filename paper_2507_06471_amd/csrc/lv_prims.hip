@@ -145,12 +145,13 @@ __global__ __launch_bounds__(256) void k_radix_hist(const K* keys, int64_t n, in
 // written out so that each digit's run of the tile lands contiguously at its
 // global offset.  counts/offsets are digit-major: offsets[d * nblocks + b] is
 // where tile b's elements with digit d start.
-template <typename K>
+// VALS = false: keys alone (vals and vals_out null).
+template <typename K, bool VALS>
 __global__ __launch_bounds__(256) void k_radix_scatter(const K* keys, const int32_t* vals, K* keys_out, int32_t* vals_out,
                                                        int64_t n, int shift, const int32_t* offsets, int nblocks)
 {
     __shared__ K s_key[RADIX_TILE];
-    __shared__ int32_t s_val[RADIX_TILE];
+    __shared__ int32_t s_val[VALS ? RADIX_TILE : 1];
     __shared__ uint32_t s_gbase[256];  // global start of each digit's run of this tile
     __shared__ uint32_t s_lbase[256];  // its start inside the tile
     __shared__ uint32_t s_run[256];    // elements of each digit placed so far
@@ -190,7 +191,8 @@ __global__ __launch_bounds__(256) void k_radix_scatter(const K* keys, const int3
         const int64_t p = base + it * 256 + t;
         const bool valid = p < n;
         const K key = valid ? keys[p] : (K)0;
-        const int32_t v = valid ? (vals ? vals[p] : (int32_t)p) : 0;  // null: each element's index
+        int32_t v = 0;
+        if constexpr (VALS) v = valid ? (vals ? vals[p] : (int32_t)p) : 0;  // null: each element's index
         const uint32_t d = (uint32_t)(key >> shift) & 255u;
         const uint64_t act = __ballot(valid);
         const uint64_t peers = match_digit(d, act);
@@ -205,7 +207,7 @@ __global__ __launch_bounds__(256) void k_radix_scatter(const K* keys, const int3
                 if ((x & 0xFFFF0000u) == tag) o += x & 0xFFFFu;
             }
             s_key[o] = key;
-            s_val[o] = v;
+            if constexpr (VALS) s_val[o] = v;
         }
         uint32_t add = 0;
 #pragma unroll
@@ -223,10 +225,11 @@ __global__ __launch_bounds__(256) void k_radix_scatter(const K* keys, const int3
         const uint32_t d = (uint32_t)(key >> shift) & 255u;
         const uint32_t g = s_gbase[d] + ((uint32_t)q - s_lbase[d]);
         keys_out[g] = key;
-        vals_out[g] = s_val[q];
+        if constexpr (VALS) vals_out[g] = s_val[q];
     }
 }
 
+// vals and vals_alt null: keys alone.
 // first (may be null): the first pass reads its keys from there, each with its
 // index as value, instead of from keys and vals; at least one pass then runs.
 template <typename K>
@@ -248,7 +251,8 @@ hipError_t radix_sort_t(K* keys, int32_t* vals, K* keys_alt, int32_t* vals_alt, 
         k_radix_hist<K><<<(unsigned)nb, 256, 0, s>>>(in_k, n, shift, counts, (int)nb);
         hipError_t e = scan_exclusive_t<int32_t>(counts, counts, nb * 256, nullptr, tmp + cbytes, tmp_bytes - cbytes, s);
         if (e != hipSuccess) return e;
-        k_radix_scatter<K><<<(unsigned)nb, 256, 0, s>>>(in_k, in_v, dst_k, dst_v, n, shift, counts, (int)nb);
+        if (dst_v) k_radix_scatter<K, true><<<(unsigned)nb, 256, 0, s>>>(in_k, in_v, dst_k, dst_v, n, shift, counts, (int)nb);
+        else k_radix_scatter<K, false><<<(unsigned)nb, 256, 0, s>>>(in_k, nullptr, dst_k, nullptr, n, shift, counts, (int)nb);
         K* tk = src_k; src_k = dst_k; dst_k = tk;
         int32_t* tv = src_v; src_v = dst_v; dst_v = tv;
         *in_alt = !*in_alt;

@@ -90,3 +90,23 @@ def test_validation_with_the_cache_left_out():
     with lvp.Graph.from_csr(g, validate=True, entry_cache=False) as dg:
         got = lvp.louvain(dg)
     assert np.array_equal(got.final_labels, oracle.louvain(g).final_labels)
+
+
+# Runs of equal keys are merged per 64-lane wavefront and per tile of 2048
+# keys: run lengths around both, one run over several tiles, nothing left after
+# the loops are dropped, and each way of counting (weights, listings, once).
+@pytest.mark.parametrize("runs", [[1], [2048], [4097], [63, 1, 64, 65], [2047, 1, 2048, 2], [1, 2049, 5000, 3],
+                                  [1] * 2047, [1] * 2049, [3] * 1366])
+@pytest.mark.parametrize("how", ["weights", "listings", "once", "loops_dropped"])
+def test_runs_of_equal_edges(runs, how):
+    n = len(runs) + 1
+    which = np.repeat(np.arange(len(runs), dtype=np.int32), runs)
+    rng = np.random.default_rng(len(runs) + runs[0])
+    rng.shuffle(which)
+    src, dst = which, (which if how == "loops_dropped" else which + 1).astype(np.int32)
+    w = rng.integers(1, 9, len(which)).astype(np.int32) if how == "weights" else None
+    flags = {"simple": how == "once", "drop_loops": how == "loops_dropped"}
+    want = oracle.graph_from_edges(n, src, dst, w, **flags)
+    with lvp.Graph.from_edges(n, src, dst, w, **flags) as g:
+        got = g.csr()
+    assert all(np.array_equal(a, b) for a, b in zip(got, want))
