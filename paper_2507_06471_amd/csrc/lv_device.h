@@ -18,6 +18,14 @@ __device__ __forceinline__ uint32_t lane_rank(uint64_t mask)
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
+// Workgroups are dispatched to the 8 XCDs round-robin; renumber them so that
+// consecutive logical ids run on one XCD (and share its L2).
+__device__ __forceinline__ int32_t xcd_logical(int32_t b, int32_t nblk)
+{
+    const int32_t x = b & 7, k = b >> 3, q = nblk >> 3, r = nblk & 7;
+    return x * q + min(x, r) + k;
+}
+
 // slot hash of a community id in an open-addressing table
 __device__ __forceinline__ uint32_t mix32(int32_t key)
 {

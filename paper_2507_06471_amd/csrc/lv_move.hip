@@ -947,14 +947,6 @@ constexpr int PSLOTS_COMPACT = 16384;  // 8-byte slots (key, weight): 128 KiB
 constexpr int BBS = 256;               // bucketed partition workgroups
 constexpr int BSLOTS = 2048;           // 12-byte slots (key, weight, volume): 24 KiB, six workgroups a CU
 
-// Workgroups are dispatched to the 8 XCDs round-robin; renumber them so that
-// consecutive logical ids run on one XCD (and share its L2).
-__device__ __forceinline__ int32_t xcd_logical(int32_t b, int32_t nblk)
-{
-    const int32_t x = b & 7, k = b >> 3, q = nblk >> 3, r = nblk & 7;
-    return x * q + min(x, r) + k;
-}
-
 // One workgroup per (vertex, partition): aggregate the partition's
 // communities in LDS (or, in the first sweep, score a contiguous 1/P of the
 // entries directly) and write the partial best.

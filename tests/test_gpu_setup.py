@@ -110,3 +110,18 @@ def test_runs_of_equal_edges(runs, how):
     with lvp.Graph.from_edges(n, src, dst, w, **flags) as g:
         got = g.csr()
     assert all(np.array_equal(a, b) for a, b in zip(got, want))
+
+
+# The sort works in wavefronts of 1024 keys, tiles of 4096 and groups of eight
+# tiles: an edge list is two keys an edge, so edge counts around half of each,
+# with and without weights moved along, and digits from one value to all.
+@pytest.mark.parametrize("m", [1, 511, 512, 513, 2047, 2048, 2049, 16383, 16384, 16385, 18433])
+@pytest.mark.parametrize("n", [2, 700, 70000])
+def test_sort_sizes(m, n):
+    rng = np.random.default_rng(m + n)
+    src, dst = rng.integers(0, n, m).astype(np.int32), rng.integers(0, n, m).astype(np.int32)
+    for w in (None, rng.integers(1, 9, m).astype(np.int32)):
+        want = oracle.graph_from_edges(n, src, dst, w)
+        with lvp.Graph.from_edges(n, src, dst, w) as g:
+            got = g.csr()
+        assert all(np.array_equal(a, b) for a, b in zip(got, want)), w is None
