@@ -1616,7 +1616,8 @@ lv_status aggregate_by_community(lv_graph* g, const LevelGraph& G, int32_t n2, i
     int32_t* wt = G.w ? col + E : nullptr;
     int32_t* col2 = (int32_t*)ws.keys_alt.p;
     int32_t* wt2 = col2 + E;
-    HIP_TRY(launch_perm_rows(n, voff, E, mem, G.off, G.idx, G.w, labels, col, wt, nullptr, nullptr, s));
+    HIP_TRY(launch_perm_rows(n, voff, E, mem, G.off, G.idx, G.w, labels, col, wt, nullptr, nullptr, nullptr,
+                             s));
     // 5. coarse vertices by segment length, with the local-moving classes'
     // bounds (the tuning's, never above a class's table)
     HIP_TRY(launch_classify(n2, seg, bounds, ws.cls.as<uint32_t>(), ws.vert.as<int32_t>(), s));
@@ -2117,7 +2118,7 @@ lv_status degree_order(lv_graph* g, int32_t n, int64_t nnz, const int32_t* off, 
     if (rank) HIP_TRY(rev2->ensure(sizeof(int32_t) * (size_t)std::max<int64_t>(nnz, 1)));
     HIP_TRY(launch_perm_rows(n, off2.as<int32_t>(), nnz, orig.as<int32_t>(), off, idx, w, inv.as<int32_t>(),
                              idx2.as<int32_t>(), w ? w2.as<int32_t>() : nullptr, rank,
-                             rank ? rev2->as<int32_t>() : nullptr, s));
+                             rank ? rev2->as<int32_t>() : nullptr, ws.keys.p, s));  // the sort keys are done with
     HIP_TRY(launch_gather_i32(k, orig.as<int32_t>(), n, k2.as<int32_t>(), s));
     HIP_TRY(hipStreamSynchronize(s));
     return LV_OK;

@@ -263,19 +263,32 @@ __global__ void k_perm_lengths(const int32_t* perm, int32_t n, const int32_t* of
         len[q] = off[v + 1] - off[v];
     }
 }
-// new row q = old row perm[q], its column positions mapped through inv
+// place[v] = (new position, new row start) of old row v: one gather an entry
+// where the reverse entries are mapped too
+__global__ void k_perm_places(const int32_t* perm, int32_t n, const int32_t* off_new, int2* place)
+{
+    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += (int64_t)gridDim.x * blockDim.x)
+        place[perm[q]] = make_int2((int32_t)q, off_new[q]);
+}
+// new row q = old row perm[q], its column positions mapped through inv, or
+// through place with the reverse entries
+template <bool REV>
 __global__ __launch_bounds__(TILE_BS) void k_perm_rows(int32_t n, const int32_t* off_new, int64_t nnz,
                                                         const int32_t* perm, const int32_t* off, const int32_t* idx,
-                                                        const int32_t* w, const int32_t* inv, int32_t* idx_new,
-                                                        int32_t* w_new, const int32_t* rank, int32_t* rev_new)
+                                                        const int32_t* w, const int32_t* inv, const int2* place,
+                                                        int32_t* idx_new, int32_t* w_new, const int32_t* rank,
+                                                        int32_t* rev_new)
 {
     for_tile_entries_co_at<TILE_BS, TILE_IT>((int64_t)blockIdx.x, off_new, n, nnz, [&](int32_t q, int64_t e) {
         const int64_t src = (int64_t)off[perm[q]] + (e - off_new[q]);
-        const int32_t p = inv[idx[src]];
-        idx_new[e] = p;
+        if constexpr (REV) {  // the reverse entry keeps its rank within its (moved) row
+            const int2 to = place[idx[src]];
+            idx_new[e] = to.x;
+            rev_new[e] = to.y + rank[src];
+        } else {
+            idx_new[e] = inv[idx[src]];
+        }
         if (w) w_new[e] = w[src];
-        // the reverse entry keeps its rank within its (moved) row
-        if (rank) rev_new[e] = off_new[p] + rank[src];
     });
 }
 
@@ -368,11 +381,17 @@ hipError_t launch_perm_lengths(const int32_t* perm, int32_t n, const int32_t* of
 }
 hipError_t launch_perm_rows(int32_t n, const int32_t* off_new, int64_t nnz, const int32_t* perm, const int32_t* off,
                             const int32_t* idx, const int32_t* w, const int32_t* inv, int32_t* idx_new, int32_t* w_new,
-                            const int32_t* rank, int32_t* rev_new, hipStream_t s)
+                            const int32_t* rank, int32_t* rev_new, void* place, hipStream_t s)
 {
     if (nnz <= 0) return hipSuccess;
-    k_perm_rows<<<tiles_for(n, nnz), TILE_BS, 0, s>>>(n, off_new, nnz, perm, off, idx, w, inv, idx_new, w_new, rank,
-                                                      rev_new);
+    if (rank) {
+        k_perm_places<<<LV_GRID(n)>>>(perm, n, off_new, (int2*)place);
+        k_perm_rows<true><<<tiles_for(n, nnz), TILE_BS, 0, s>>>(n, off_new, nnz, perm, off, idx, w, nullptr,
+                                                                (const int2*)place, idx_new, w_new, rank, rev_new);
+    } else {
+        k_perm_rows<false><<<tiles_for(n, nnz), TILE_BS, 0, s>>>(n, off_new, nnz, perm, off, idx, w, inv, nullptr,
+                                                                 idx_new, w_new, nullptr, nullptr);
+    }
     return hipGetLastError();
 }
 hipError_t launch_export_rows(int32_t n, const int32_t* off_out, int64_t nnz, const int32_t* inv, const int32_t* orig,

@@ -396,10 +396,11 @@ hipError_t launch_max_degree(int32_t n, const int32_t* off, int32_t* out, hipStr
 hipError_t launch_inverse(const int32_t* perm, int32_t n, int32_t* inv, hipStream_t s);
 hipError_t launch_perm_lengths(const int32_t* perm, int32_t n, const int32_t* off, int32_t* len, hipStream_t s);
 // rank (may be null): the reverse-entry ranks of the old rows (launch_reverse_check);
-// then rev_new receives the reverse-entry map of the permuted CSR
+// then rev_new receives the reverse-entry map of the permuted CSR, inv is not
+// read (it is perm's inverse) and place is scratch of 8 n bytes
 hipError_t launch_perm_rows(int32_t n, const int32_t* off_new, int64_t nnz, const int32_t* perm, const int32_t* off,
                             const int32_t* idx, const int32_t* w, const int32_t* inv, int32_t* idx_new, int32_t* w_new,
-                            const int32_t* rank, int32_t* rev_new, hipStream_t s);
+                            const int32_t* rank, int32_t* rev_new, void* place, hipStream_t s);
 // a stored CSR in id order (off_out: its row offsets), loops halved; w_out may be null
 hipError_t launch_export_rows(int32_t n, const int32_t* off_out, int64_t nnz, const int32_t* inv, const int32_t* orig,
                               const int32_t* off, const int32_t* idx, const int32_t* w, int32_t* idx_out,
