@@ -2463,9 +2463,11 @@ static lv_status reorder_by_degree(lv_graph* g, const int32_t* rank)
 // graph g at vertices [voff[g], voff[g+1])): validation, loop doubling,
 // degrees, per-graph M and singleton Q_int.  trusted: a CSR the library has
 // built itself (offsets, sorted columns and weights are not checked again).
+// own_idx, own_w (may be null): buffers that hold indices and weights, taken
+// over instead of copied.
 static lv_status graph_setup(lv_graph* g, int32_t n, const int32_t* offsets, const int32_t* indices,
                              const int32_t* weights, lv_memkind kind, uint32_t flags, const std::vector<int32_t>& voff,
-                             bool trusted = false)
+                             bool trusted = false, DevBuf* own_idx = nullptr, DevBuf* own_w = nullptr)
 {
     hipStream_t s = g->stream;
     LV_TRY(ensure_pinned(g, 4096));
@@ -2484,20 +2486,21 @@ static lv_status graph_setup(lv_graph* g, int32_t n, const int32_t* offsets, con
     g->nnz = nnz;
     g->G = G;
     g->voff = voff;
-    // one slab for the set-up: the given arrays, the order by column and the
-    // reverse ranks per entry (then, in the order's place, the stored arrays
+    // one slab for the set-up: the given arrays and the order by column per
+    // entry (then, in the order's place, the reverse ranks, the stored arrays
     // and the reverse map), the storage order per vertex
     const bool order = (flags & LV_VALIDATE) || !(flags & LV_NO_ENTRY_CACHE);
-    g->arena->reserve((size_t)nnz * ((weights ? 8 : 4) + (order ? 16 : 8) + ((flags & LV_NO_ENTRY_CACHE) ? 0 : 4)) +
-                      64 * (size_t)n + (64 << 10));
+    g->arena->reserve((size_t)nnz * ((own_idx ? 0 : weights ? 8 : 4) + (order ? 16 : 8)) + 64 * (size_t)n + (64 << 10));
+    if (own_idx) g->idx.swap(*own_idx);
+    if (own_w) g->w.swap(*own_w);
     HIP_TRY(g->idx.ensure(sizeof(int32_t) * (size_t)std::max<int64_t>(nnz, 1)));
-    if (nnz > 0) HIP_TRY(hipMemcpyAsync(g->idx.p, indices, sizeof(int32_t) * (size_t)nnz, hk, s));
+    if (nnz > 0 && !own_idx) HIP_TRY(hipMemcpyAsync(g->idx.p, indices, sizeof(int32_t) * (size_t)nnz, hk, s));
     Workspace& ws = g->ws;
     HIP_TRY(ws.small.ensure(4096));
     int32_t* d_err = ws.small.as<int32_t>();
     HIP_TRY(hipMemsetAsync(d_err, 0, 16, s));
     if (weights) HIP_TRY(g->w.ensure(sizeof(int32_t) * (size_t)std::max<int64_t>(nnz, 1)));
-    if (weights && nnz > 0) HIP_TRY(hipMemcpyAsync(g->w.p, weights, sizeof(int32_t) * (size_t)nnz, hk, s));
+    if (weights && nnz > 0 && !own_w) HIP_TRY(hipMemcpyAsync(g->w.p, weights, sizeof(int32_t) * (size_t)nnz, hk, s));
     HIP_TRY(launch_check_offsets(n, g->off.as<int32_t>(), nnz, d_err, s));
     int32_t err = 0;
     HIP_TRY(hipMemcpyAsync(&err, d_err, sizeof err, hipMemcpyDeviceToHost, s));
@@ -2520,15 +2523,14 @@ static lv_status graph_setup(lv_graph* g, int32_t n, const int32_t* offsets, con
     if (nnz > 0 && (want_rank || (flags & LV_VALIDATE))) {
         DevBuf ck(g->arena), cv(g->arena), ck2(g->arena), cv2(g->arena);
         for (DevBuf* b : {&ck, &cv, &ck2, &cv2}) HIP_TRY(b->ensure(sizeof(int32_t) * (size_t)nnz));
-        if (want_rank) HIP_TRY(rank.ensure(sizeof(int32_t) * (size_t)nnz));
         HIP_TRY(ws.tmp.ensure(radix_tmp_bytes(nnz)));
         bool alt = false;
         HIP_TRY(radix_order_u32((const uint32_t*)g->idx.p, ck.as<uint32_t>(), cv.as<int32_t>(), ck2.as<uint32_t>(),
                                 cv2.as<int32_t>(), nnz, bits_for(std::max(n, 2)), ws.tmp.p, ws.tmp.cap, &alt, s));
         const bool val = (flags & LV_VALIDATE) != 0;
+        rank.swap(alt ? cv2 : cv);  // each reverse entry gives way to its rank
         HIP_TRY(launch_reverse_check(n, g->off.as<int32_t>(), g->idx.as<int32_t>(), val ? w_in : nullptr, nnz,
-                                     alt ? cv2.as<int32_t>() : cv.as<int32_t>(),
-                                     alt ? ck2.as<int32_t>() : ck.as<int32_t>(),
+                                     rank.as<int32_t>(), alt ? ck2.as<int32_t>() : ck.as<int32_t>(),
                                      want_rank ? rank.as<int32_t>() : nullptr, val ? 8 : 32, 8, d_err, s));
         HIP_TRY(hipMemcpyAsync(&err, d_err, sizeof err, hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
@@ -2725,10 +2727,9 @@ static lv_status create_from_edges(lv_graph* g, int32_t n, int64_t m, const int3
     const int cb = bits_for((int64_t)n + 1);
     const int64_t E = 2 * m;
     const bool unit = (flags & LV_EDGES_SIMPLE) != 0;
-    // one slab for the larger of the sort (keys and weights with their
-    // alternates, the merged CSR) and the set-up that follows (that CSR, its
-    // copy, the entries' order by column with its alternate, the ranks)
-    g->arena->reserve((size_t)E * (unit ? 28 : 36) + 64 * (size_t)n + (64 << 10));
+    // one slab: the keys and weights with their alternates and the merged CSR;
+    // the set-up that follows takes the CSR over and its memory from there
+    g->arena->reserve((size_t)E * (weights ? 32 : unit ? 20 : 24) + 64 * (size_t)n + (64 << 10));
     LV_TRY(sort_workspace(g, E, weights != nullptr));
     int64_t* d_stats = (int64_t*)(ws.small.as<char>() + 3840);
     int32_t* d_err = ws.small.as<int32_t>();
@@ -2756,7 +2757,8 @@ static lv_status create_from_edges(lv_graph* g, int32_t n, int64_t m, const int3
     d_w.release();
     release_sort_workspace(g);
     return graph_setup(g, n, off.as<int32_t>(), idx.as<int32_t>(), unit ? nullptr : w.as<int32_t>(), LV_MEM_DEVICE,
-                       flags & (LV_KEEP_ORDER | LV_NO_ENTRY_CACHE), std::vector<int32_t>{0, n}, true);
+                       flags & (LV_KEEP_ORDER | LV_NO_ENTRY_CACHE), std::vector<int32_t>{0, n}, true, &idx,
+                       unit ? nullptr : &w);
 }
 
 lv_status lv_graph_create_edges(int32_t n, int64_t m, const int32_t* src, const int32_t* dst, const int32_t* weights,

@@ -319,7 +319,7 @@ __global__ __launch_bounds__(TILE_BS) void k_export_rows(int32_t n, const int32_
 // column j come out in the order of their rows, and the t-th of them is the
 // reverse of row j's t-th entry.  rev[e] = the listed entry and col[e] its
 // column, as sorted: the entry is checked to lie in row idx[e], to point back,
-// and (w not null) to have the same weight; rank[e] (may be null) = its
+// and (w not null) to have the same weight; rank[e] (null, or rev itself, too) = its
 // position in that row.  Structural mismatches set structural_bits in err,
 // weight mismatches weight_bits.  Three sorting passes and one gather per entry
 // replace a binary search for each of them (twice: once to validate, once for
