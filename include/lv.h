@@ -108,7 +108,8 @@ typedef enum lv_memkind { LV_MEM_HOST = 0, LV_MEM_DEVICE = 1 } lv_memkind;
                           /* whose pair changed; a sweep then streams the array instead of gathering */
                           /* one pair per entry at random.  Results are identical either way.       */
                           /* Needs the handle's reverse-entry map (not LV_NO_ENTRY_CACHE); off with */
-                          /* LV_PRUNE and LV_ASYNC.                                                  */
+                          /* LV_PRUNE and LV_ASYNC, and on graphs of fewer than 2^22 entries unless */
+                          /* lv_tuning.cache_pct is given.                                          */
 
 typedef struct lv_graph lv_graph;   /* device-resident CSR + workspace, library-owned */
 typedef struct lv_result lv_result; /* per-level labels and statistics, library-owned */
@@ -144,8 +145,9 @@ typedef struct lv_tuning {
                         /* longest sorted), sorting otherwise.  Same coarse graphs.       */
     int32_t cache_pct;  /* entry cache: the next sweep reads the cache when at most this  */
                         /* percentage of the level's entries saw their pair change in the */
-                        /* last commit (0 = 10, at most 100); a sweep fills it when at    */
-                        /* most min(100, 2 cache_pct + 5) percent changed                  */
+                        /* last commit (0 = 10, and no cache on graphs of fewer than 2^22 */
+                        /* entries; at most 100); a sweep fills it when at most           */
+                        /* min(100, 2 cache_pct + 5) percent changed                       */
     int32_t fused;      /* later sweeps: 1 = every class below block_max in one persistent */
                         /* launch (1024-thread workgroups taking blocks of rows of any    */
                         /* class from a device counter); 0 = one launch per class          */
