@@ -1856,13 +1856,14 @@ lv_status coarsen(lv_graph* g, const LevelGraph& G, const SweepOut& so, int slot
     HIP_TRY(ws.a_cnt.ensure(nb));
     HIP_TRY(ws.g_idx[slot].ensure(sizeof(int32_t) * (size_t)G.nnz));
     HIP_TRY(ws.g_w[slot].ensure(sizeof(int32_t) * (size_t)G.nnz));
-    const size_t old_cap = ws.ht_keys.cap;
-    const void* old_p = ws.ht_keys.p;
-    HIP_TRY(ws.ht_keys.ensure(sizeof(unsigned long long) * slots));
-    HIP_TRY(ws.ht_vals.ensure(ws.ht_keys.cap / 2));
     // the row pass empties every slot it reads, so the table is cleared only
-    // when it is new or an aggregation did not complete
-    if (!ws.ht_clean || ws.ht_keys.cap != old_cap || ws.ht_keys.p != old_p)
+    // when it is new or an aggregation did not complete; marked before it may
+    // grow, so that an allocation that fails leaves nothing taken for cleared
+    const size_t key_bytes = sizeof(unsigned long long) * slots;
+    if (ws.ht_keys.cap < key_bytes) ws.ht_clean = false;
+    HIP_TRY(ws.ht_keys.ensure(key_bytes));
+    HIP_TRY(ws.ht_vals.ensure(ws.ht_keys.cap / 2));
+    if (!ws.ht_clean)
         HIP_TRY(launch_hash_clear(ws.ht_keys.as<unsigned long long>(), ws.ht_vals.as<int32_t>(),
                                   (int64_t)(ws.ht_keys.cap / sizeof(unsigned long long)), s));
     ws.ht_clean = false;
