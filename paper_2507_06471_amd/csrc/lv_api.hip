@@ -3129,17 +3129,17 @@ static lv_status modularity_impl(lv_graph* g, const int32_t* labels_dev, int64_t
     const int32_t n = g->n;
     *q_int = 0;
     if (n == 0) return LV_OK;
-    HIP_TRY(ws.k64.ensure(256 + sizeof(int32_t) * (size_t)n));
+    HIP_TRY(ws.k64.ensure(256 + sizeof(int64_t) * (size_t)n));
     if (g->reordered) HIP_TRY(ws.pos.ensure(sizeof(int32_t) * ((size_t)n + 1)));
     LV_TRY(ensure_pinned(g, 4096));
     void* dp = nullptr;
     HIP_TRY(hipHostGetDevicePointer(&dp, g->pinned, 0));
     ModMail* mail = (ModMail*)g->pinned;
     mail->ready = 0;
-    HIP_TRY(launch_fill_i32(ws.k64.as<int32_t>(), 0, 64 + (int64_t)n, s));
+    HIP_TRY(launch_fill_i32(ws.k64.as<int32_t>(), 0, 64 + 2 * (int64_t)n, s));
     HIP_TRY(launch_modularity(n, g->off.as<int32_t>(), g->idx.as<int32_t>(), g->weighted ? g->w.as<int32_t>() : nullptr,
                               g->nnz, g->k.as<int32_t>(), labels_dev, g->reordered ? g->orig.as<int32_t>() : nullptr,
-                              ws.pos.as<int32_t>(), ws.k64.as<int32_t>() + 64, ws.k64.as<ModSums>(), (ModMail*)dp, s));
+                              ws.pos.as<int32_t>(), ws.k64.as<int64_t>() + 32, ws.k64.as<ModSums>(), (ModMail*)dp, s));
     LV_TRY(await_flag(s, &mail->ready));
     if (mail->err) { set_error_msg("labels must lie in [0, n)"); return LV_E_ARG; }
     *q_int = g->M[0] * mail->sums[0] - mail->sums[1];

@@ -204,12 +204,12 @@ __global__ __launch_bounds__(TILE_BS) void k_sigma_in_cached(int32_t n, const in
 // The sum of squared volumes, added to out->sums[1]; the last workgroup posts
 // all three results to pinned memory (mail null: not), in the launch that
 // finds them.
-__global__ __launch_bounds__(256) void k_mod_finish(const int32_t* vol, int64_t n, ModSums* out, ModMail* mail)
+__global__ __launch_bounds__(256) void k_mod_finish(const int64_t* vol, int64_t n, ModSums* out, ModMail* mail)
 {
     __shared__ unsigned long long red[4];
     unsigned long long s = 0;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
-        s += (unsigned long long)((int64_t)vol[i] * vol[i]);
+        s += (unsigned long long)(vol[i] * vol[i]);
     s = block_sum<256>(s, red);
     if (threadIdx.x != 0) return;
     if (s) atomicAdd((unsigned long long*)&out->sums[1], s);
@@ -507,7 +507,7 @@ hipError_t launch_sigma_in_cached(int32_t n, const int32_t* off, const int2* ce,
     return hipGetLastError();
 }
 hipError_t launch_modularity(int32_t n, const int32_t* off, const int32_t* idx, const int32_t* w, int64_t nnz,
-                             const int32_t* k, const int32_t* labels, const int32_t* orig, int32_t* pos, int32_t* vol,
+                             const int32_t* k, const int32_t* labels, const int32_t* orig, int32_t* pos, int64_t* vol,
                              ModSums* out, ModMail* mail, hipStream_t s)
 {
     hipError_t e = launch_mod_volumes(n, k, labels, orig, pos, vol, &out->err, s);

@@ -451,9 +451,9 @@ struct ModMail {
     int32_t err, ready;
 };
 hipError_t launch_mod_volumes(int32_t n, const int32_t* k, const int32_t* labels, const int32_t* orig, int32_t* pos,
-                              int32_t* vol, int32_t* err, hipStream_t s);
+                              int64_t* vol, int32_t* err, hipStream_t s);
 hipError_t launch_modularity(int32_t n, const int32_t* off, const int32_t* idx, const int32_t* w, int64_t nnz,
-                             const int32_t* k, const int32_t* labels, const int32_t* orig, int32_t* pos, int32_t* vol,
+                             const int32_t* k, const int32_t* labels, const int32_t* orig, int32_t* pos, int64_t* vol,
                              ModSums* out, ModMail* mail, hipStream_t s);
 
 // ---- small levels (lv_small.hip)

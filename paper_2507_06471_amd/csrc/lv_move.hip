@@ -549,8 +549,9 @@ constexpr int APPLY_SLOTS = 4096;
 constexpr int APPLY_PROBE = 16;
 constexpr int APPLY_FILL = APPLY_SLOTS * 3 / 4;
 
-__device__ __forceinline__ void apply_add(int32_t* key, int32_t* val, int32_t* fill, int32_t* sigma, int32_t C,
-                                          int32_t d)
+// V: int32_t, or unsigned long long for sums held in 64 bits.
+template <typename V>
+__device__ __forceinline__ void apply_add(int32_t* key, V* val, int32_t* fill, V* sigma, int32_t C, V d)
 {
     // a community already in the table always adds there; a new one takes
     // a slot only while the table holds fewer than APPLY_FILL communities
@@ -574,15 +575,15 @@ __device__ __forceinline__ void apply_add(int32_t* key, int32_t* val, int32_t* f
 // valid lane's community are summed into one add (movers crowding into one
 // large community), every other lane adds on its own (the LDS atomics sort
 // out any further collisions).  Reached by all lanes of the wavefront.
-__device__ __forceinline__ void peeled_apply(int32_t* key, int32_t* val, int32_t* fill, int32_t* sigma, int32_t C,
-                                             int32_t d, bool valid)
+template <typename V>
+__device__ __forceinline__ void peeled_apply(int32_t* key, V* val, int32_t* fill, V* sigma, int32_t C, V d, bool valid)
 {
     const uint64_t any = __ballot(valid);
     if (!any) return;
     const int leader = __ffsll((unsigned long long)any) - 1;
     const int32_t lc = __shfl(C, leader);
     const bool mine = valid && C == lc;
-    int32_t c = mine ? d : 0;
+    V c = mine ? d : (V)0;
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) c += __shfl_xor(c, m);
     if ((int)lane_id() == leader && c) apply_add(key, val, fill, sigma, lc, c);
@@ -1478,13 +1479,13 @@ __global__ __launch_bounds__(256) void k_volumes(const int32_t* verts, int32_t m
 
 // Modularity's pass over the vertices: each one's label, by position where
 // rows are stored out of id order; labels outside [0, n) flagged and left out;
-// vol[label] += k (summed per workgroup as above; volumes are below 2^31, as
-// the library rejects a larger total).
+// vol[label] += k, in 64 bits throughout (summed per workgroup as above).
 __global__ __launch_bounds__(256) void k_mod_volumes(int32_t n, const int32_t* k, const int32_t* labels,
-                                                     const int32_t* orig, int32_t* pos, int32_t* vol, int32_t* err)
+                                                     const int32_t* orig, int32_t* pos, unsigned long long* vol,
+                                                     int32_t* err)
 {
     __shared__ int32_t t_key[APPLY_SLOTS];
-    __shared__ int32_t t_val[APPLY_SLOTS];
+    __shared__ unsigned long long t_val[APPLY_SLOTS];
     __shared__ int32_t t_fill;
     if (threadIdx.x == 0) t_fill = 0;
     for (int t = threadIdx.x; t < APPLY_SLOTS; t += 256) { t_key[t] = EMPTY_KEY; t_val[t] = 0; }
@@ -1500,7 +1501,7 @@ __global__ __launch_bounds__(256) void k_mod_volumes(int32_t n, const int32_t* k
             if (orig) pos[i] = C;
             bad = bad || C < 0 || C >= n;
         }
-        peeled_apply(t_key, t_val, &t_fill, vol, C, kv, in && C >= 0 && C < n);
+        peeled_apply(t_key, t_val, &t_fill, vol, C, (unsigned long long)kv, in && C >= 0 && C < n);
     }
     if (bad) atomicOr(err, 1);
     __syncthreads();
@@ -2046,10 +2047,10 @@ hipError_t launch_apply(const int32_t* verts, const int32_t* dec, int32_t m, con
     return hipGetLastError();
 }
 hipError_t launch_mod_volumes(int32_t n, const int32_t* k, const int32_t* labels, const int32_t* orig, int32_t* pos,
-                              int32_t* vol, int32_t* err, hipStream_t s)
+                              int64_t* vol, int32_t* err, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    k_mod_volumes<<<grid_for(n, 1024, 2048), 256, 0, s>>>(n, k, labels, orig, pos, vol, err);
+    k_mod_volumes<<<grid_for(n, 1024, 2048), 256, 0, s>>>(n, k, labels, orig, pos, (unsigned long long*)vol, err);
     return hipGetLastError();
 }
 hipError_t launch_volumes(const int32_t* verts, int32_t m, const int32_t* k, const int32_t* comm, int32_t* sigma,
