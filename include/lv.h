@@ -405,7 +405,10 @@ lv_status lv_modularity_noalloc(lv_graph* g, const int32_t* labels, int64_t* q_i
  * jobs that continue together with the graphs staged since, and runs one
  * Louvain level (Algorithm 3) for all of them in the same launches.  Each job
  * keeps its own M, stopping rule and acceptance, so its partition equals
- * lv_louvain's on its graph alone.  A device-resident submission's copy is
+ * lv_louvain's on its graph alone.  Device memory of finished jobs is kept for
+ * the next ones, at most an eighth of the budget and 4 GiB; it counts against
+ * the budget like the estimates, and is given back when the budget or any of
+ * the server's allocations needs it.  A device-resident submission's copy is
  * not counted in the budget.  Every server call is thread-safe; results are
  * kept until lv_server_result.
  * ------------------------------------------------------------------------- */

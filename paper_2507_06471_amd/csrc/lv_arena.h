@@ -1,0 +1,299 @@
+// Device memory of handles and servers: fault injection, slabs that finished
+// jobs leave to the next ones, arenas and the buffers cut from them.
+#pragma once
+
+#include <hip/hip_runtime_api.h>
+
+#include <algorithm>
+#include <cstddef>
+#include <cstdint>
+#include <cstdlib>
+#include <map>
+#include <memory>
+#include <mutex>
+#include <vector>
+
+namespace lv {
+
+// Allocation with optional fault injection for tests of the out-of-memory
+// paths: with LV_FAULT_ALLOC_AT=k in the environment, the k-th device or
+// pinned-host allocation made by one entry-point call on the calling thread
+// fails with out-of-memory.  The variable is read at the start of every
+// graph-creation, louvain, lpa and modularity call (FaultScope), so a test may
+// change it between calls.
+inline thread_local long t_alloc_count = 0;
+inline thread_local long t_fail_at = 0;
+struct FaultScope {
+    FaultScope()
+    {
+        t_alloc_count = 0;
+        const char* v = std::getenv("LV_FAULT_ALLOC_AT");
+        t_fail_at = v ? std::atol(v) : 0L;
+    }
+};
+inline bool fault_now()
+{
+    ++t_alloc_count;
+    return t_fail_at > 0 && t_alloc_count == t_fail_at;
+}
+inline hipError_t dev_alloc(void** p, size_t bytes)
+{
+    if (fault_now()) { *p = nullptr; return hipErrorOutOfMemory; }
+    return hipMalloc(p, bytes ? bytes : 1);
+}
+
+// Device memory that arenas take from and give back to.  Owned by a server
+// (its jobs' graphs come and go): keeps at most `bound` bytes of slabs for the
+// next job and frees them when it is destroyed, when the server's budget needs
+// them (shrink) and when any of the server's allocations finds no memory.
+struct Slab {
+    char* p = nullptr;
+    size_t size = 0;
+};
+class SlabCache {
+public:
+    explicit SlabCache(size_t bound) : bound_(bound) {}
+    ~SlabCache() { flush(); }
+    SlabCache(const SlabCache&) = delete;
+    SlabCache& operator=(const SlabCache&) = delete;
+    // the smallest kept slab of at least `bytes` (and at most four times that)
+    bool take(size_t bytes, Slab& out)
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        int best = -1;
+        for (int t = 0; t < (int)kept_.size(); ++t)
+            if (kept_[t].size >= bytes && kept_[t].size / 4 <= bytes && (best < 0 || kept_[t].size < kept_[best].size))
+                best = t;
+        if (best < 0) return false;
+        out = kept_[best];
+        held_ -= out.size;
+        kept_.erase(kept_.begin() + best);
+        return true;
+    }
+    void put(const Slab& sl)
+    {
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            if (held_ + sl.size <= bound_) {
+                kept_.push_back(sl);
+                held_ += sl.size;
+                return;
+            }
+        }
+        (void)hipFree(sl.p);
+    }
+    void flush() { shrink(0); }
+    // free slabs until at most `bytes` are kept, the largest first
+    void shrink(size_t bytes)
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        while (held_ > bytes) {
+            const auto big = std::max_element(kept_.begin(), kept_.end(),
+                                              [](const Slab& a, const Slab& b) { return a.size < b.size; });
+            (void)hipFree(big->p);
+            held_ -= big->size;
+            kept_.erase(big);
+        }
+    }
+    size_t held()
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        return held_;
+    }
+
+private:
+    std::mutex mu_;
+    std::vector<Slab> kept_;
+    size_t held_ = 0;
+    const size_t bound_;
+};
+
+// The device memory of one handle: a few large slabs that its buffers are cut
+// from (first fit by size, neighbours joined when freed), given back when the
+// handle goes.  A run on a fresh handle made some 85 allocations, and freeing
+// a block of 4 MiB or more costs 0.2-0.9 ms each (the device is drained and
+// the block unmapped): of the 38 ms that a job of 16 M entries took from host
+// arrays to host labels, 18 were spent there.  Every buffer of an arena is used on the
+// handle's stream (a freed block's next user is ordered after its last) or
+// after the host has waited for that stream.
+// cache: slabs come from there and go back there (share), or it is only emptied
+// when there is no memory (not share: a server's worker, which keeps its slabs).
+class Arena {
+public:
+    explicit Arena(std::shared_ptr<SlabCache> cache = nullptr, bool share = true)
+        : cache_(std::move(cache)), share_(share && cache_)
+    {
+    }
+    ~Arena()
+    {
+        for (auto& r : slabs_) {
+            if (share_) cache_->put(r.slab);
+            else (void)hipFree(r.slab.p);
+        }
+    }
+    Arena(const Arena&) = delete;
+    Arena& operator=(const Arena&) = delete;
+    // `high`: from the end of the free block (long-lived buffers), so that the
+    // short-lived ones leave one hole, not many.  bytes: a multiple of 256.
+    hipError_t alloc(size_t bytes, bool high, void** out)
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        if (carve(bytes, high, out)) return hipSuccess;
+        // grow by half of what is held, at least 1 MiB and at most 256 MiB more than asked for
+        const size_t extra = std::min<size_t>(std::max<size_t>(held_ / 2, MIN_SLAB), (size_t)256 << 20);
+        hipError_t e = grow(std::max(bytes, extra));
+        if (e == hipErrorOutOfMemory) e = grow(bytes);
+        if (e != hipSuccess) return e;
+        return carve(bytes, high, out) ? hipSuccess : hipErrorOutOfMemory;
+    }
+    void free(void* p, size_t bytes)
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        for (auto& r : slabs_) {
+            if ((char*)p < r.slab.p || (char*)p >= r.slab.p + r.slab.size) continue;
+            size_t at = (size_t)((char*)p - r.slab.p);
+            auto nx = r.free.lower_bound(at);
+            if (nx != r.free.end() && at + bytes == nx->first) {
+                bytes += nx->second;
+                nx = r.free.erase(nx);
+            }
+            if (nx != r.free.begin()) {
+                auto pv = std::prev(nx);
+                if (pv->first + pv->second == at) {
+                    pv->second += bytes;
+                    return;
+                }
+            }
+            r.free.emplace(at, bytes);
+            return;
+        }
+    }
+    // Make sure that about `bytes` are free, in one more slab if they are not
+    // (a hint: a failure is left to the allocations that follow).
+    void reserve(size_t bytes)
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        size_t have = 0;
+        for (auto& r : slabs_)
+            for (auto& f : r.free) have += f.second;
+        if (have < bytes) (void)grow(bytes - have);
+    }
+
+    // bytes of slabs taken from the cache beyond what was asked for
+    size_t surplus()
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        return surplus_;
+    }
+
+private:
+    static constexpr size_t MIN_SLAB = (size_t)1 << 20;
+    struct Region {
+        Slab slab;
+        std::map<size_t, size_t> free;  // offset -> length, no two adjacent
+    };
+    bool carve(size_t bytes, bool high, void** out)
+    {
+        Region* br = nullptr;
+        std::map<size_t, size_t>::iterator best;
+        for (auto& r : slabs_)
+            for (auto it = r.free.begin(); it != r.free.end(); ++it)
+                if (it->second >= bytes && (!br || it->second < best->second)) {
+                    br = &r;
+                    best = it;
+                }
+        if (!br) return false;
+        const size_t at = best->first, len = best->second;
+        if (high) {
+            *out = br->slab.p + at + (len - bytes);
+            if (len == bytes) br->free.erase(best);
+            else best->second = len - bytes;
+        } else {
+            *out = br->slab.p + at;
+            br->free.erase(best);
+            if (len > bytes) br->free.emplace(at + bytes, len - bytes);
+        }
+        return true;
+    }
+    hipError_t grow(size_t bytes)
+    {
+        bytes = (std::max(bytes, MIN_SLAB) + 0xFFFFF) & ~(size_t)0xFFFFF;
+        Region r;
+        if (share_ && cache_->take(bytes, r.slab)) {
+            surplus_ += r.slab.size - bytes;
+        } else {
+            void* p = nullptr;
+            hipError_t e = hipMalloc(&p, bytes);
+            if (e == hipErrorOutOfMemory && cache_) {
+                cache_->flush();
+                (void)hipGetLastError();
+                e = hipMalloc(&p, bytes);
+            }
+            if (e != hipSuccess) {
+                (void)hipGetLastError();
+                return e;
+            }
+            r.slab.p = (char*)p;
+            r.slab.size = bytes;
+        }
+        held_ += r.slab.size;
+        r.free.emplace(0, r.slab.size);
+        slabs_.push_back(std::move(r));
+        return hipSuccess;
+    }
+    std::mutex mu_;
+    std::vector<Region> slabs_;
+    size_t held_ = 0;
+    size_t surplus_ = 0;
+    std::shared_ptr<SlabCache> cache_;
+    const bool share_;
+};
+
+// Grow-only device buffer, of an arena or (without one) an allocation of its own.
+struct DevBuf {
+    void* p = nullptr;
+    size_t cap = 0;
+    std::shared_ptr<Arena> arena;  // where the next allocation comes from
+    bool high = false;
+    std::shared_ptr<Arena> from;   // where p came from
+    DevBuf() = default;
+    explicit DevBuf(std::shared_ptr<Arena> a, bool high_ = false) : arena(std::move(a)), high(high_) {}
+    DevBuf(const DevBuf&) = delete;
+    DevBuf& operator=(const DevBuf&) = delete;
+    ~DevBuf() { release(); }
+    void release()
+    {
+        if (p) {
+            if (from) from->free(p, cap);
+            else (void)hipFree(p);
+        }
+        p = nullptr;
+        cap = 0;
+        from.reset();
+    }
+    hipError_t ensure(size_t bytes)
+    {
+        bytes = (bytes + 255) & ~(size_t)255;
+        if (bytes == 0) bytes = 256;
+        if (cap >= bytes) return hipSuccess;
+        release();
+        hipError_t e;
+        if (arena) {
+            e = fault_now() ? hipErrorOutOfMemory : arena->alloc(bytes, high, &p);
+            if (e == hipSuccess) from = arena;
+        } else {
+            e = dev_alloc(&p, bytes);
+        }
+        if (e == hipSuccess) cap = bytes; else p = nullptr;
+        return e;
+    }
+    template <typename T> T* as() const { return (T*)p; }
+    void swap(DevBuf& o)
+    {
+        std::swap(p, o.p);
+        std::swap(cap, o.cap);
+        std::swap(from, o.from);
+    }
+};
+
+}  // namespace lv
