@@ -11,6 +11,7 @@
 #include <map>
 #include <memory>
 #include <mutex>
+#include <new>
 #include <vector>
 
 namespace lv {
@@ -74,10 +75,13 @@ public:
     {
         {
             std::lock_guard<std::mutex> lk(mu_);
-            if (held_ + sl.size <= bound_) {
-                kept_.push_back(sl);
-                held_ += sl.size;
-                return;
+            try {
+                if (held_ + sl.size <= bound_) {
+                    kept_.push_back(sl);
+                    held_ += sl.size;
+                    return;
+                }
+            } catch (const std::bad_alloc&) {  // no host memory to keep it by
             }
         }
         (void)hipFree(sl.p);
@@ -115,7 +119,8 @@ private:
 // the block unmapped): of the 38 ms that a job of 16 M entries took from host
 // arrays to host labels, 18 were spent there.  Every buffer of an arena is used on the
 // handle's stream (a freed block's next user is ordered after its last) or
-// after the host has waited for that stream.
+// after the host has waited for that stream.  Running out of host memory is
+// out-of-memory like any other: nothing here throws.
 // cache: slabs come from there and go back there (share), or it is only emptied
 // when there is no memory (not share: a server's worker, which keeps its slabs).
 class Arena {
@@ -164,7 +169,10 @@ public:
                     return;
                 }
             }
-            r.free.emplace(at, bytes);
+            try {
+                r.free.emplace(at, bytes);
+            } catch (const std::bad_alloc&) {  // unused until the arena goes
+            }
             return;
         }
     }
@@ -210,8 +218,12 @@ private:
             else best->second = len - bytes;
         } else {
             *out = br->slab.p + at;
-            br->free.erase(best);
-            if (len > bytes) br->free.emplace(at + bytes, len - bytes);
+            auto node = br->free.extract(best);
+            if (len > bytes) {
+                node.key() = at + bytes;
+                node.mapped() = len - bytes;
+                br->free.insert(std::move(node));
+            }
         }
         return true;
     }
@@ -219,6 +231,12 @@ private:
     {
         bytes = (std::max(bytes, MIN_SLAB) + 0xFFFFF) & ~(size_t)0xFFFFF;
         Region r;
+        try {  // all the host memory it takes, before the device's
+            slabs_.reserve(slabs_.size() + 1);
+            r.free.emplace(0, 0);
+        } catch (const std::bad_alloc&) {
+            return hipErrorOutOfMemory;
+        }
         if (share_ && cache_->take(bytes, r.slab)) {
             surplus_ += r.slab.size - bytes;
         } else {
@@ -237,7 +255,7 @@ private:
             r.slab.size = bytes;
         }
         held_ += r.slab.size;
-        r.free.emplace(0, r.slab.size);
+        r.free.begin()->second = r.slab.size;
         slabs_.push_back(std::move(r));
         return hipSuccess;
     }

@@ -5,6 +5,16 @@
 
 using namespace lv;
 
+// the fail_new-th allocation from now on fails
+void* operator new(std::size_t n)
+{
+    if (device().fail_new >= 0 && !device().inside && device().fail_new-- == 0) throw std::bad_alloc();
+    if (void* p = std::malloc(n)) return p;
+    throw std::bad_alloc();
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, std::size_t) noexcept { std::free(p); }
+
 #define CHECK(c)                                                         \
     do {                                                                 \
         if (!(c)) {                                                      \
@@ -77,9 +87,37 @@ int shrink_to_the_budget()
     return 0;
 }
 
+// Host memory that runs out in the middle of any of these is an error code or
+// nothing at all, never an exception, and no device memory is lost.
+int host_memory_runs_out()
+{
+    device().limit = 100 * MiB;
+    for (int k = 0; k < 12; ++k) {
+        auto cache = std::make_shared<SlabCache>(80 * MiB);
+        {
+            auto arena = std::make_shared<Arena>(cache);
+            DevBuf a(arena), b(arena, true), c(arena), d(arena);
+            device().fail_new = k;
+            const hipError_t e = a.ensure(2 * MiB);
+            CHECK(e == hipSuccess || e == hipErrorOutOfMemory);
+            arena->reserve(8 * MiB);
+            for (DevBuf* q : {&b, &c, &d}) (void)q->ensure(MiB);
+            c.release();
+            b.release();
+            device().fail_new = -1;
+            CHECK(a.ensure(2 * MiB) == hipSuccess && c.ensure(MiB) == hipSuccess);
+            device().fail_new = k > 6 ? 0 : -1;  // while the slabs go to the cache
+        }
+        device().fail_new = -1;
+    }
+    CHECK(device().used == 0);
+    return 0;
+}
+
 int main()
 {
-    const int r = worker_empties_the_cache() + surplus_is_reported() + shrink_to_the_budget();
+    const int r = worker_empties_the_cache() + surplus_is_reported() + shrink_to_the_budget() +
+                  host_memory_runs_out();
     if (r == 0 && device().used == 0) std::printf("ok\n");
     return r == 0 && device().used == 0 ? 0 : 1;
 }

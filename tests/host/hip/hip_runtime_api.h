@@ -11,7 +11,8 @@ constexpr hipError_t hipSuccess = 0, hipErrorOutOfMemory = 2;
 struct FakeDevice {
     std::map<void*, std::size_t> live;
     std::size_t used = 0, limit = ~(std::size_t)0;
-    int mallocs = 0;
+    int fail_new = -1;    // host allocations left until one fails (tests)
+    bool inside = false;  // the allocations of these functions do not count
 };
 inline FakeDevice& device()
 {
@@ -23,9 +24,10 @@ inline hipError_t hipMalloc(void** p, std::size_t n)
     FakeDevice& d = device();
     if (d.used + n > d.limit) { *p = nullptr; return hipErrorOutOfMemory; }
     *p = std::malloc(n);
+    d.inside = true;
     d.live[*p] = n;
+    d.inside = false;
     d.used += n;
-    ++d.mallocs;
     return hipSuccess;
 }
 inline hipError_t hipFree(void* p)
