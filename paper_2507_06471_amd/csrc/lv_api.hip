@@ -99,6 +99,16 @@ struct Workspace {
         for (int q = 0; q < 2; ++q)
             for (DevBuf* b : {&g_off[q], &g_idx[q], &g_w[q], &g_k[q], &g_gid[q]}) b->arena = a;
     }
+    // every buffer back to the arena
+    void reset()
+    {
+        hub_table_clean = ht_clean = false;
+#define LV_X(b) b.release();
+        LV_WORKSPACE_BUFFERS(LV_X)
+#undef LV_X
+        for (int q = 0; q < 2; ++q)
+            for (DevBuf* b : {&g_off[q], &g_idx[q], &g_w[q], &g_k[q], &g_gid[q]}) b->release();
+    }
 };
 
 struct Timer {
@@ -1926,7 +1936,7 @@ lv_status louvain_impl(lv_graph* g, const Params& p, bool keep_graphs, lv_result
     // staging arrays and the first coarse graph, per vertex the sweep and
     // renumbering arrays
     if (!g->run_reserved) {
-        g->arena->reserve((size_t)g->nnz * 32 + 96 * (size_t)g->n + (64 << 10));
+        g->arena->reserve(0, (size_t)g->nnz * 32 + 96 * (size_t)g->n + (64 << 10));
         g->run_reserved = true;  // the buffers of the first run serve the later ones
     }
     LevelGraph G = level0(g);
@@ -2223,6 +2233,8 @@ static lv_status graph_setup(lv_graph* g, int32_t n, const int32_t* offsets, con
     hipStream_t s = g->stream;
     LV_TRY(ensure_pinned(g, 4096));
     const hipMemcpyKind hk = kind == LV_MEM_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice;
+    const bool as_given = flags & LV_KEEP_ORDER;  // the given arrays are the stored ones
+    for (DevBuf* b : {&g->off, &g->idx, &g->w, &g->k}) b->keep = as_given;
     HIP_TRY(g->off.ensure(sizeof(int32_t) * ((size_t)n + 1)));
     HIP_TRY(hipMemcpyAsync(g->off.p, offsets, sizeof(int32_t) * ((size_t)n + 1), hk, s));
     int32_t first_last[2];
@@ -2237,11 +2249,16 @@ static lv_status graph_setup(lv_graph* g, int32_t n, const int32_t* offsets, con
     g->nnz = nnz;
     g->G = G;
     g->voff = voff;
-    // one slab for the set-up: the given arrays and the order by column per
-    // entry (then, in the order's place, the reverse ranks, the stored arrays
-    // and the reverse map), the storage order per vertex
-    const bool order = (flags & LV_VALIDATE) || !(flags & LV_NO_ENTRY_CACHE);
-    g->arena->reserve((size_t)nnz * ((own_idx ? 0 : weights ? 8 : 4) + (order ? 16 : 8)) + 64 * (size_t)n + (64 << 10));
+    // Set-up's memory: what the handle keeps (the stored arrays, the reverse
+    // map, per vertex the storage order) and the rest (the given arrays, the
+    // order by column and the reverse ranks in its place).  Three of the four
+    // arrays of the order lie where the stored arrays come to lie.
+    const bool cache = !(flags & LV_NO_ENTRY_CACHE), order = (flags & LV_VALIDATE) || cache;
+    const size_t given = weights ? 8 : 4, keep = given + (cache ? 4 : 0);
+    const size_t scratch = as_given ? (!order ? 0 : cache ? 12 : 16)
+                                    : (own_idx ? 0 : given) + (order ? std::max<size_t>(16 - keep, 4) : 0);
+    g->arena->reserve((size_t)nnz * keep + 20 * (size_t)n + (64 << 10),
+                      (size_t)nnz * scratch + 64 * (size_t)n + (order ? radix_tmp_bytes(nnz) : 0) + (64 << 10));
     if (own_idx) g->idx.swap(*own_idx);
     if (own_w) g->w.swap(*own_w);
     HIP_TRY(g->idx.ensure(sizeof(int32_t) * (size_t)std::max<int64_t>(nnz, 1)));
@@ -2272,12 +2289,16 @@ static lv_status graph_setup(lv_graph* g, int32_t n, const int32_t* offsets, con
     bool rank_ok = false;
     const bool want_rank = !(flags & LV_NO_ENTRY_CACHE) && nnz > 0;
     if (nnz > 0 && (want_rank || (flags & LV_VALIDATE))) {
-        DevBuf ck(g->arena), cv(g->arena), ck2(g->arena), cv2(g->arena);
-        for (DevBuf* b : {&ck, &cv, &ck2, &cv2}) HIP_TRY(b->ensure(sizeof(int32_t) * (size_t)nnz));
+        const int bits = bits_for(std::max(n, 2));
+        const bool ends_in_alt = (bits + 7) / 8 % 2 != 0;  // passes of 8 bits
+        // the order that becomes the ranks away from what is kept, the rest there
+        DevBuf ck(g->arena, true), cv(g->arena, ends_in_alt), ck2(g->arena, true), cv2(g->arena, !ends_in_alt);
+        for (DevBuf* b : {ends_in_alt ? &cv2 : &cv, ends_in_alt ? &cv : &cv2, &ck, &ck2})
+            HIP_TRY(b->ensure(sizeof(int32_t) * (size_t)nnz));
         HIP_TRY(ws.tmp.ensure(radix_tmp_bytes(nnz)));
         bool alt = false;
         HIP_TRY(radix_order_u32((const uint32_t*)g->idx.p, ck.as<uint32_t>(), cv.as<int32_t>(), ck2.as<uint32_t>(),
-                                cv2.as<int32_t>(), nnz, bits_for(std::max(n, 2)), ws.tmp.p, ws.tmp.cap, &alt, s));
+                                cv2.as<int32_t>(), nnz, bits, ws.tmp.p, ws.tmp.cap, &alt, s));
         const bool val = (flags & LV_VALIDATE) != 0;
         rank.swap(alt ? cv2 : cv);  // each reverse entry gives way to its rank
         HIP_TRY(launch_reverse_check(n, g->off.as<int32_t>(), g->idx.as<int32_t>(), val ? w_in : nullptr, nnz,
@@ -2362,6 +2383,14 @@ static lv_status graph_setup(lv_graph* g, int32_t n, const int32_t* offsets, con
     }
     g->has_rev = rank_ok;
     return LV_OK;
+}
+
+// Set-up's scratch memory back to the device.  An idle handle then holds 8 to
+// 12 bytes an entry, where set-up takes 20 to 36: a program may hold many.
+static void settle(lv_graph* g)
+{
+    g->ws.reset();
+    g->arena->trim();
 }
 
 static lv_status new_graph(void* stream, lv_graph** out, std::shared_ptr<SlabCache> cache = nullptr, bool share = true)
@@ -2477,11 +2506,17 @@ static lv_status create_from_edges(lv_graph* g, int32_t n, int64_t m, const int3
     }
     const int cb = bits_for((int64_t)n + 1);
     const int64_t E = 2 * m;
-    const bool unit = (flags & LV_EDGES_SIMPLE) != 0;
-    // one slab: the keys and weights with their alternates and the merged CSR;
-    // the set-up that follows takes the CSR over and its memory from there
-    g->arena->reserve((size_t)E * (weights ? 32 : unit ? 20 : 24) + 64 * (size_t)n + (64 << 10));
+    const bool unit = (flags & LV_EDGES_SIMPLE) != 0, as_given = flags & LV_KEEP_ORDER;
+    // The keys and weights with their alternates and the merged CSR; the
+    // set-up that follows takes the CSR over and its memory from there.  The
+    // alternates lie where the stored arrays come to lie.
+    const size_t keep = (unit ? 4 : 8) + (flags & LV_NO_ENTRY_CACHE ? 0 : 4), all = weights ? 32 : unit ? 20 : 24;
+    g->arena->reserve((size_t)E * keep + 20 * (size_t)n + (64 << 10),
+                      (size_t)E * (as_given ? (weights ? 24 : 16) : std::max<size_t>(all - keep, unit ? 12 : weights ? 20 : 16)) +
+                          64 * (size_t)n + radix_tmp_bytes(E) + (64 << 10));
+    ws.keys_alt.keep = ws.vals_alt.keep = !as_given;
     LV_TRY(sort_workspace(g, E, weights != nullptr));
+    ws.keys_alt.keep = ws.vals_alt.keep = false;
     int64_t* d_stats = (int64_t*)(ws.small.as<char>() + 3840);
     int32_t* d_err = ws.small.as<int32_t>();
     HIP_TRY(hipMemsetAsync(d_stats, 0, 2 * sizeof(int64_t), s));
@@ -2502,7 +2537,7 @@ static lv_status create_from_edges(lv_graph* g, int32_t n, int64_t m, const int3
         set_error_msg("total volume M >= 2^31");
         return LV_E_OVERFLOW;
     }
-    DevBuf off(g->arena), idx(g->arena), w(g->arena);
+    DevBuf off(g->arena), idx(g->arena, as_given), w(g->arena, as_given);
     int64_t nnz = 0;
     LV_TRY(csr_from_keys(g, E, stats[0], cb, n, weights != nullptr, !unit, off, idx, w, nnz));
     d_w.release();
@@ -2536,6 +2571,7 @@ lv_status lv_graph_create_edges(int32_t n, int64_t m, const int32_t* src, const 
         delete g;
         return st;
     }
+    settle(g);
     *out = g;
     return LV_OK;
 }
@@ -2609,6 +2645,7 @@ lv_status lv_graph_create_csr(int32_t n, const int32_t* offsets, const int32_t* 
         delete g;
         return st;
     }
+    settle(g);
     *out = g;
     return LV_OK;
 }
@@ -2670,6 +2707,7 @@ lv_status lv_graph_create_batch(int32_t count, const int32_t* n, const int32_t* 
         delete g;
         return st;
     }
+    settle(g);
     *out = g;
     return LV_OK;
 }

@@ -113,7 +113,7 @@ private:
 };
 
 // The device memory of one handle: a few large slabs that its buffers are cut
-// from (first fit by size, neighbours joined when freed), given back when the
+// from (best fit, neighbours joined when freed), given back when the
 // handle goes.  A run on a fresh handle made some 85 allocations, and freeing
 // a block of 4 MiB or more costs 0.2-0.9 ms each (the device is drained and
 // the block unmapped): of the 38 ms that a job of 16 M entries took from host
@@ -138,18 +138,21 @@ public:
     }
     Arena(const Arena&) = delete;
     Arena& operator=(const Arena&) = delete;
-    // `high`: from the end of the free block (long-lived buffers), so that the
-    // short-lived ones leave one hole, not many.  bytes: a multiple of 256.
-    hipError_t alloc(size_t bytes, bool high, void** out)
+    // `keep`: a buffer that the handle keeps between calls, or one that is gone
+    // before those come.  They and the others (scratch) come from slabs of
+    // their own as far as those have room, and from the end of a free block, so
+    // that trim() finds the scratch slabs empty.  bytes: a multiple of 256.
+    hipError_t alloc(size_t bytes, bool keep, void** out)
     {
         std::lock_guard<std::mutex> lk(mu_);
-        if (carve(bytes, high, out)) return hipSuccess;
-        // grow by half of what is held, at least 1 MiB and at most 256 MiB more than asked for
-        const size_t extra = std::min<size_t>(std::max<size_t>(held_ / 2, MIN_SLAB), (size_t)256 << 20);
-        hipError_t e = grow(std::max(bytes, extra));
-        if (e == hipErrorOutOfMemory) e = grow(bytes);
+        if (carve(bytes, keep, out)) return hipSuccess;
+        // scratch grows by half of what is held, at least 1 MiB and at most 256 MiB at a time
+        // (by an eighth: a job of 16 M entries 15.3 ms, 14.4 so)
+        const size_t extra = keep ? 0 : std::min<size_t>(std::max<size_t>(held_ / 2, MIN_SLAB), (size_t)256 << 20);
+        hipError_t e = grow(std::max(bytes, extra), keep);
+        if (e == hipErrorOutOfMemory) e = grow(bytes, keep);
         if (e != hipSuccess) return e;
-        return carve(bytes, high, out) ? hipSuccess : hipErrorOutOfMemory;
+        return carve(bytes, keep, out) ? hipSuccess : hipErrorOutOfMemory;
     }
     void free(void* p, size_t bytes)
     {
@@ -176,17 +179,50 @@ public:
             return;
         }
     }
-    // Make sure that about `bytes` are free, in one more slab if they are not
-    // (a hint: a failure is left to the allocations that follow).
-    void reserve(size_t bytes)
+    // Make sure that about `keep` and `scratch` bytes are free for either kind,
+    // in one more slab each if they are not (a hint: a failure is left to the
+    // allocations that follow).  Little memory, and that of a server's job,
+    // comes as one slab: there is nothing to trim.
+    void reserve(size_t keep, size_t scratch)
     {
         std::lock_guard<std::mutex> lk(mu_);
-        size_t have = 0;
+        size_t have[2] = {0, 0};
         for (auto& r : slabs_)
-            for (auto& f : r.free) have += f.second;
-        if (have < bytes) (void)grow(bytes - have);
+            for (auto& f : r.free) have[r.keep] += f.second;
+        if (share_ || keep + scratch <= TRIM_MIN) {
+            have[0] += have[1];
+            scratch += keep;
+            keep = 0;
+        }
+        if (have[1] < keep) (void)grow(keep - have[1], true);
+        if (have[0] < scratch) (void)grow(scratch - have[0], false);
     }
-
+    // Give slabs without a buffer in them back to the device, if that is more
+    // than TRIM_MIN bytes.  Everything queued on the handle's stream is done.
+    void trim()
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        const auto empty = [](const Region& r) { return r.free.size() == 1 && r.free.begin()->second == r.slab.size; };
+        size_t unused = 0;
+        for (auto& r : slabs_)
+            if (empty(r)) unused += r.slab.size;
+        if (share_ || unused <= TRIM_MIN) return;
+        for (auto it = slabs_.begin(); it != slabs_.end();) {
+            if (empty(*it)) {
+                (void)hipFree(it->slab.p);
+                held_ -= it->slab.size;
+                it = slabs_.erase(it);
+            } else {
+                ++it;
+            }
+        }
+    }
+    // bytes of its slabs, used and free
+    size_t held()
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        return held_;
+    }
     // bytes of slabs taken from the cache beyond what was asked for
     size_t surplus()
     {
@@ -196,23 +232,29 @@ public:
 
 private:
     static constexpr size_t MIN_SLAB = (size_t)1 << 20;
+    static constexpr size_t TRIM_MIN = (size_t)8 << 20;
     struct Region {
         Slab slab;
+        bool keep = false;
         std::map<size_t, size_t> free;  // offset -> length, no two adjacent
     };
-    bool carve(size_t bytes, bool high, void** out)
+    // the smallest free block that fits, of a slab of the same kind if there is one
+    bool carve(size_t bytes, bool keep, void** out)
     {
         Region* br = nullptr;
         std::map<size_t, size_t>::iterator best;
         for (auto& r : slabs_)
-            for (auto it = r.free.begin(); it != r.free.end(); ++it)
-                if (it->second >= bytes && (!br || it->second < best->second)) {
+            for (auto it = r.free.begin(); it != r.free.end(); ++it) {
+                if (it->second < bytes) continue;
+                const bool kind = r.keep == keep, best_kind = br && br->keep == keep;
+                if (!br || (kind && !best_kind) || (kind == best_kind && it->second < best->second)) {
                     br = &r;
                     best = it;
                 }
+            }
         if (!br) return false;
         const size_t at = best->first, len = best->second;
-        if (high) {
+        if (keep) {
             *out = br->slab.p + at + (len - bytes);
             if (len == bytes) br->free.erase(best);
             else best->second = len - bytes;
@@ -227,7 +269,7 @@ private:
         }
         return true;
     }
-    hipError_t grow(size_t bytes)
+    hipError_t grow(size_t bytes, bool keep)
     {
         bytes = (std::max(bytes, MIN_SLAB) + 0xFFFFF) & ~(size_t)0xFFFFF;
         Region r;
@@ -256,6 +298,7 @@ private:
         }
         held_ += r.slab.size;
         r.free.begin()->second = r.slab.size;
+        r.keep = keep;
         slabs_.push_back(std::move(r));
         return hipSuccess;
     }
@@ -272,10 +315,10 @@ struct DevBuf {
     void* p = nullptr;
     size_t cap = 0;
     std::shared_ptr<Arena> arena;  // where the next allocation comes from
-    bool high = false;
+    bool keep = false;             // see Arena::alloc
     std::shared_ptr<Arena> from;   // where p came from
     DevBuf() = default;
-    explicit DevBuf(std::shared_ptr<Arena> a, bool high_ = false) : arena(std::move(a)), high(high_) {}
+    explicit DevBuf(std::shared_ptr<Arena> a, bool keep_ = false) : arena(std::move(a)), keep(keep_) {}
     DevBuf(const DevBuf&) = delete;
     DevBuf& operator=(const DevBuf&) = delete;
     ~DevBuf() { release(); }
@@ -297,7 +340,7 @@ struct DevBuf {
         release();
         hipError_t e;
         if (arena) {
-            e = fault_now() ? hipErrorOutOfMemory : arena->alloc(bytes, high, &p);
+            e = fault_now() ? hipErrorOutOfMemory : arena->alloc(bytes, keep, &p);
             if (e == hipSuccess) from = arena;
         } else {
             e = dev_alloc(&p, bytes);

@@ -54,14 +54,14 @@ int surplus_is_reported()
     auto cache = std::make_shared<SlabCache>(80 * MiB);
     for (size_t first : {40 * MiB, 12 * MiB}) {
         auto job = std::make_shared<Arena>(cache);
-        job->reserve(first);
+        job->reserve(0, first);
         CHECK(job->surplus() == (first == 40 * MiB ? 0 : 28 * MiB));
     }
     auto small = std::make_shared<Arena>(cache);
-    small->reserve(9 * MiB);  // a slab of more than four times the request stays where it is
+    small->reserve(0, 9 * MiB);  // a slab of more than four times the request stays where it is
     CHECK(small->surplus() == 0 && cache->held() == 40 * MiB);
     auto alone = std::make_shared<Arena>();
-    alone->reserve(5 * MiB);
+    alone->reserve(0, 5 * MiB);
     CHECK(alone->surplus() == 0);
     return 0;
 }
@@ -73,9 +73,9 @@ int shrink_to_the_budget()
     auto cache = std::make_shared<SlabCache>(90 * MiB);
     {
         auto a = std::make_shared<Arena>(cache), b = std::make_shared<Arena>(cache), c = std::make_shared<Arena>(cache);
-        a->reserve(10 * MiB);
-        b->reserve(30 * MiB);
-        c->reserve(20 * MiB);
+        a->reserve(0, 10 * MiB);
+        b->reserve(0, 30 * MiB);
+        c->reserve(0, 20 * MiB);
     }
     CHECK(cache->held() == 60 * MiB);
     cache->shrink(60 * MiB);
@@ -84,6 +84,39 @@ int shrink_to_the_budget()
     CHECK(cache->held() == 30 * MiB && device().used == 30 * MiB);
     cache->shrink(0);
     CHECK(cache->held() == 0 && device().used == 0);
+    return 0;
+}
+
+// Buffers that are kept and those that are not lie in slabs of their own as far
+// as these have room; trimming frees the slabs that are empty then.
+int scratch_is_trimmed()
+{
+    device().limit = 100 * MiB;
+    auto arena = std::make_shared<Arena>();
+    DevBuf kept(arena, true), given(arena), over(arena, true), more(arena);
+    arena->reserve(8 * MiB, 20 * MiB);
+    CHECK(device().live.size() == 2 && arena->held() == 28 * MiB);
+    CHECK(given.ensure(8 * MiB) == hipSuccess && over.ensure(8 * MiB) == hipSuccess);
+    CHECK(more.ensure(12 * MiB) == hipSuccess && device().live.size() == 2);
+    over.release();  // the kept buffer takes its place
+    CHECK(kept.ensure(8 * MiB) == hipSuccess && device().live.size() == 2);
+    arena->trim();
+    CHECK(arena->held() == 28 * MiB);
+    more.release();
+    given.release();
+    arena->trim();
+    CHECK(arena->held() == 8 * MiB && device().used == 8 * MiB);
+    CHECK(given.ensure(3 * MiB) == hipSuccess);  // of a new slab
+    given.release();
+    arena->trim();  // too little to be worth a call
+    CHECK(device().live.size() == 2);
+    auto small = std::make_shared<Arena>();
+    small->reserve(3 * MiB, 5 * MiB);
+    CHECK(device().live.size() == 3);
+    auto job = std::make_shared<Arena>(std::make_shared<SlabCache>(MiB));
+    job->reserve(10 * MiB, 10 * MiB);  // a server's job: one slab, nothing trimmed
+    job->trim();
+    CHECK(device().live.size() == 4 && job->held() == 20 * MiB);
     return 0;
 }
 
@@ -100,7 +133,7 @@ int host_memory_runs_out()
             device().fail_new = k;
             const hipError_t e = a.ensure(2 * MiB);
             CHECK(e == hipSuccess || e == hipErrorOutOfMemory);
-            arena->reserve(8 * MiB);
+            arena->reserve(0, 8 * MiB);
             for (DevBuf* q : {&b, &c, &d}) (void)q->ensure(MiB);
             c.release();
             b.release();
@@ -116,7 +149,7 @@ int host_memory_runs_out()
 
 int main()
 {
-    const int r = worker_empties_the_cache() + surplus_is_reported() + shrink_to_the_budget() +
+    const int r = worker_empties_the_cache() + surplus_is_reported() + shrink_to_the_budget() + scratch_is_trimmed() +
                   host_memory_runs_out();
     if (r == 0 && device().used == 0) std::printf("ok\n");
     return r == 0 && device().used == 0 ? 0 : 1;
