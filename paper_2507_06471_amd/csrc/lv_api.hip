@@ -1176,7 +1176,9 @@ lv_status run_sweeps(lv_graph* g, const LevelGraph& G, int mode, const Params& p
     // compulsory bytes of a sweep: 8 per CSR entry (index and weight) and 36
     // per vertex (offsets, label, degree and volume read; label and volume written)
     out.bytes = (8 * G.nnz + 36 * (int64_t)n) * out.executed;
+    const int32_t hub_launches = 2 + (hubs.args.bucketed && hubs.args.nsc > 0 ? 1 : 0) + (hubs.args.nins > 0 ? 3 : 0);
     for (int32_t sw = 1; sw <= out.executed; ++sw) {
+        if ((small || merge_thin) && fmap.nclass > 0) out.launches += 1;  // its classes: see merged below
         const bool fused_sweep = fused && sw > 1 && fmap.nclass > 0;  // the classes below the hub class in one launch
         if (fused_sweep) {
             out.launches += 1;
@@ -1192,7 +1194,8 @@ lv_status run_sweeps(lv_graph* g, const LevelGraph& G, int mode, const Params& p
                 if (timing) out.kern_bytes[SLOT_FUSED] += 8 * cls_entries[c] + 36 * (int64_t)nv;
                 continue;
             }
-            out.launches += c == CLS_HUB ? (sw == 1 ? 2 : 2 + (hubs.args.bucketed && hubs.args.nsc > 0 ? 1 : 0) + (hubs.args.nins > 0 ? 3 : 0)) : 1;
+            const bool merged = c < CLS_HUB && (small || (merge_thin && thin[c]));
+            if (!merged) out.launches += c < CLS_HUB ? 1 : sw == 1 && !small ? 2 : hub_launches;
             if (!timing) continue;
             const int slot = 2 * c + (sw == 1 ? 1 : 0) - 2;
             const std::vector<hipEvent_t>& E = ev[sw - 1];

@@ -72,3 +72,19 @@ def test_repeated_calls_reuse_result_buffers():
         assert free_bytes(torch) == before
     assert np.array_equal(first.final_labels, want.final_labels)
     h.close()
+
+
+def test_move_launches_counts_launches():
+    # small levels: one launch a sweep whatever the classes; at 2^22 entries or more, one for the
+    # classes that are merged (here 220,000 rows of 20 to 21 entries and one of 220)
+    small = graphgen.sbm(3000, 125, 0.06, 0.001, seed=2)
+    n = 220000
+    u = np.concatenate([np.tile(np.arange(n), 10), np.zeros(200, dtype=np.int64)])
+    v = np.concatenate([(np.tile(np.arange(n), 10) + np.repeat(np.arange(1, 11), n)) % n, 1000 + 7 * np.arange(200)])
+    large = graphgen.from_edges(n, u, v)
+    assert large.nnz >= 1 << 22 and len(np.unique(np.diff(large.offsets))) == 3
+    for g in (small, large):
+        with lvp.Graph.from_csr(g) as dg:
+            levels = lvp.louvain(dg).levels
+        for i, lv in enumerate(levels if g is small else levels[:1]):
+            assert lv.info["move_launches"] == len(lv.moves), (g.n, i)
