@@ -86,7 +86,8 @@ typedef enum lv_memkind { LV_MEM_HOST = 0, LV_MEM_DEVICE = 1 } lv_memkind;
 #define LV_TIMING 1u      /* record per-kernel HIP event times (see lv_level_info); sweeps */
                           /* are then launched one by one instead of from a HIP graph     */
 #define LV_KEEP_GRAPHS 2u /* lv_louvain keeps every coarse graph for lv_result_level_graph */
-#define LV_NO_HIPGRAPH 4u /* launch sweeps one by one even without LV_TIMING              */
+#define LV_NO_HIPGRAPH 4u /* launch sweeps one by one even without LV_TIMING (levels of  */
+                          /* fewer than 2^22 entries launch them one by one anyway)      */
 #define LV_AUTOTUNE 8u    /* with tuning == NULL: use the handle's autotuned setting (lv_autotune), */
                            /* chosen on the handle's first such call                               */
 #define LV_PRUNE 16u      /* active-vertex pruning (Alg. 1's V_active, Alg. 2's needCheck), read   */

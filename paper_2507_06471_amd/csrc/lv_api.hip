@@ -5,10 +5,11 @@
 // One engine serves every entry point: a handle packs G >= 1 independent
 // graphs into one CSR (vertex segments), and every level runs all of them in
 // the same launches.  Each graph keeps its own total volume M, its own sweep
-// count and stopping rule (kept on the device: no host round trip per sweep,
-// so a level's sweep loop is replayed from a captured HIP graph), its own
-// level acceptance, and leaves the packed graph once its run ends.  A single
-// graph is the case G = 1.
+// count and stopping rule (kept on the device: no host round trip per sweep;
+// a small level's two launches a sweep are issued a few sweeps ahead, a large
+// level's sweep is captured and replayed as a HIP graph), its own level
+// acceptance, and leaves the packed graph once its run ends.  A single graph is
+// the case G = 1.
 #include "lv.h"
 #include "lv_arena.h"
 #include "lv_internal.h"
@@ -660,12 +661,18 @@ lv_status plan_hubs(lv_graph* g, const LevelGraph& G, const int32_t* hub_verts, 
 
 
 // Levels of fewer entries run their sweeps as two launches each (see
-// run_sweeps).  There the number of launches is the cost: 20 LPA sweeps of a
-// 10 K-vertex R-MAT graph took 1.10 ms with a launch per class and take 0.42 ms
-// so.  On large levels the 1024-thread workgroups of the merged kernel wait for
-// their slowest group and hide less latency: 8.1 ms for 20 sweeps of a
-// 30.5 M-entry level against 6.1 ms with a launch per class, and 130 against
-// 81 ms at 509 M entries.  Between 4 M and 16 M entries both are alike.
+// run_sweeps), without the entry cache.  There the number of launches is the
+// cost: 20 LPA sweeps of a 10 K-vertex R-MAT graph took 1.10 ms with a launch
+// per class and take 0.42 ms so.  On large levels the 1024-thread workgroups of
+// the merged kernel wait for their slowest group and hide less latency: 8.1 ms
+// for 20 sweeps of a 30.5 M-entry level against 6.1 ms with a launch per class,
+// and 130 against 81 ms at 509 M entries.  Between 4 M and 16 M entries both
+// are alike.  Entries decide, not vertices, although the gathered pairs (8
+// bytes a vertex) leave an XCD's 4 MiB L2 at 2^19 vertices: just below the line,
+// 20 Louvain sweeps with a launch per class and the cache against two launches
+// take 1.97 / 1.82 ms (R-MAT, 0.26 M vertices), 2.23 / 2.56 (random, 0.69 M),
+// 2.40 / 2.49 (random, 1 M), 2.47 / 1.80 (grid, 1 M), 3.06 / 2.25 (road-like,
+// 1.6 M), 3.19 / 2.22 (random, 2 M), and LPA 0.68-1.36 / 0.75-1.34.
 constexpr int64_t SMALL_NNZ = (int64_t)1 << 22;
 constexpr int32_t SMALL_LAG = 3;  // sweeps launched ahead of the last one known to be done
 
@@ -833,8 +840,8 @@ lv_status run_sweeps(lv_graph* g, const LevelGraph& G, int mode, const Params& p
     // Entry cache: on the handle's input graph (its reverse-entry map
     // exists), for full synchronous sweeps.  The device decides per sweep
     // whether to read, fill or bypass it (k_sweep_end).  Below SMALL_NNZ
-    // entries the gathered pairs stay in an XCD's 4 MiB L2 and the cache only
-    // adds launches, so it is left to an explicit cache_pct.
+    // entries its launches cost more than it saves (figures there), so it is
+    // left to an explicit cache_pct.
     const bool use_ec = G.rev && G.nnz > 0 && active > 0 && !(p.flags & (LV_NO_CACHE | LV_PRUNE | LV_ASYNC)) &&
                         (G.nnz >= SMALL_NNZ || p.tune.cache_forced);
     // Small levels: two launches a sweep (k_move_merged and the pair refresh),
